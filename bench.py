@@ -52,7 +52,7 @@ KERNEL_SOURCES = ("csrc/spatial.h", "csrc/aba_lane.h", "csrc/dual.h", "csrc/abad
 
 
 CONTACT_SOURCES = ("csrc/spatial.h", "csrc/dual.h", "csrc/contact_step.h", "csrc/contact_adjoint.h",
-                   "csrc/contact.hip", "_build.py")
+                   "csrc/aba_lane.h", "csrc/contact_wave.h", "csrc/contact.hip", "_build.py")
 
 
 def _hash(sources):

@@ -473,17 +473,11 @@ int sim_pgs_adjoint(int dtype, int batch, int n, int niter, const void *A, const
 #define SIM_CONTACT_MAX_LINKS 16
 #define SIM_CONTACT_MAX_SPHERES 4
 
-/* Launch geometry of the contact kernels.  Every system is one lane; this
- * chooses how many share a wavefront: rollout_systems_per_wave in {8, 4, 2}
- * (two wavefronts per workgroup in FP32, one in FP64; each system's
- * articulated quantities sit in LDS), grad_systems_per_wave in {16, 8, 4}
- * (one wavefront per workgroup), and where the gradient keeps each
- * system's Gauss-Seidel and articulated working copies: grad_lds = 1 in LDS
- * (at most 16 systems per CU at a time), 0 in private memory (every system
- * in flight at once; only with 16 systems per wavefront).  Fewer per
- * wavefront spread a small batch over more CUs.  Every geometry computes
- * the same results bit for bit; sim_contact_autotune picks the fastest for
- * a batch. */
+/* Launch geometry of the contact kernels.  They have one (16 lanes per
+ * system, four systems per wavefront), so every accepted choice runs the same
+ * launch and gives the same bits; the values are those accepted so far:
+ * rollout_systems_per_wave in {8, 4, 2}, grad_systems_per_wave in {16, 8, 4}
+ * with grad_lds = 1, or 16 with grad_lds = 0. */
 typedef struct {
   int rollout_systems_per_wave;
   int grad_systems_per_wave;
@@ -502,7 +496,7 @@ typedef struct {
   const double *limits;               /* nullable [4 n]: joint limits (lo, hi, k, d) of the
                                          1-dof joints, shared by the batch, as in
                                          sim_params (ignored for the free root) */
-  const sim_contact_tiling_t *tiling; /* nullable: 8 and 16 systems per wavefront, LDS */
+  const sim_contact_tiling_t *tiling; /* nullable */
 } sim_contact_model;
 
 /* Sizes of the model's state, control and parameter vectors (each output
@@ -545,17 +539,15 @@ int sim_contact_rollout_grad(const sim_contact_model *m, int dtype, int batch, c
                              const void *tau, double dt, int T, const void *gqT, const void *gqdT, void *gq0,
                              void *gqd0, void *gtau, void *gmu, void *stream);
 
-/* Launch-geometry autotuner for the contact kernels: times T_probe steps of
- * sim_contact_rollout from (q0, qd0) under tau (DEVICE [T_probe][nu][batch])
- * and their sim_contact_rollout_grad at every geometry of
- * sim_contact_tiling_t, on the caller's model, parameters and batch, and
- * writes the fastest of each to *chosen (m->tiling is ignored) and their
- * ms per probe step (nullable).  The probe should start from a state like
- * the ones the calls will see: a step in contact costs several times one in
- * free flight.  A set-up call, unlike the others: it
- * allocates its probe buffers with hipMalloc, frees them, and synchronises
- * `stream`.  Errors as for the rollout, SIM_ERR_HIP when the probe buffers
- * cannot be allocated. */
+/* Times T_probe steps of sim_contact_rollout from (q0, qd0) under tau (DEVICE
+ * [T_probe][nu][batch]) and their sim_contact_rollout_grad on the caller's
+ * model, parameters and batch; writes the launch geometry (one of those
+ * sim_contact_tiling_t accepts) to *chosen (m->tiling is ignored) and the ms
+ * per probe step of each (nullable).  The probe should start from a state
+ * like the ones the calls will see: a step in contact costs several times one
+ * in free flight.  A set-up call, unlike the others: it allocates its probe
+ * buffers with hipMalloc, frees them, and synchronises `stream`.  Errors as
+ * for the rollout, SIM_ERR_HIP when the probe buffers cannot be allocated. */
 int sim_contact_autotune(const sim_contact_model *m, int dtype, int batch, const void *params, const void *q0,
                          const void *qd0, const void *tau, double dt, int T_probe, void *stream,
                          sim_contact_tiling_t *chosen, double *rollout_ms, double *grad_ms);

@@ -86,8 +86,8 @@ class ContactBatch:
 
     @property
     def tiling(self) -> dict:
-        """Systems per wavefront of the rollout and of the gradient kernels,
-        and whether the gradient keeps its working copies in LDS."""
+        """The launch geometry passed with the model (every accepted choice
+        runs the same launch)."""
         return {"rollout_systems_per_wave": self._tiling.rollout_systems_per_wave,
                 "grad_systems_per_wave": self._tiling.grad_systems_per_wave, "grad_lds": self._tiling.grad_lds}
 
@@ -101,9 +101,9 @@ class ContactBatch:
         self._tiling.grad_lds = int(grad_lds)
 
     def autotune(self, q0, qd0, tau, dt) -> dict:
-        """Times T = tau.shape[0] probe steps of the rollout and its gradient at
-        every launch geometry (sim_contact_autotune), keeps the fastest and
-        returns it with the ms per probe step of each kernel."""
+        """Times T = tau.shape[0] probe steps of the rollout and its gradient
+        (sim_contact_autotune); returns the launch geometry with the ms per
+        probe step of each kernel."""
         T = int(tau.shape[0])
         self._check(q0, (self.nq, self.B), "q0")
         self._check(qd0, (self.nv, self.B), "qd0")

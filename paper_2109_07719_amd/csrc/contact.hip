@@ -19,17 +19,13 @@
 //     (p1 = p + dt R v_lin1 and the normalised quaternion step for a free
 //     root, q1 = q + dt qd1 for 1-dof joints).
 //
-// Design: the forward runs one lane per system, a few systems to a wave, and
-// keeps the whole tree's articulated quantities in LDS (the gradient keeps
-// them in private memory, see k_contact_adj).  J comes from the
-// world poses and joint axes along the contact link's path to the root;
-// each column of M^-1 J^T is the articulated-body response to a unit force
-// at the contact point (passes 2 and 3 of the ABA with the factorisation
-// of the step's own pass 2 reused, no velocity or gravity terms).  The
-// gradient runs backwards in time, also one lane per system: each step is
-// recomputed from the stored state, then its statements are reversed
-// (contact_adjoint.h), and the adjoint of the state is carried to the
-// previous step (Sec. 3, Eq. adj_back; Sec. 4.1, Eq. adj_r).
+// Design: 16 lanes per system (contact_wave.h says why).  The gradient runs
+// backwards in time in the same layout: each step is recomputed from the
+// stored state, then its statements are reversed, and the adjoint of the
+// state is carried to the previous step (Sec. 3, Eq. adj_back; Sec. 4.1, Eq.
+// adj_r).  contact_step.h and contact_adjoint.h hold the same step and its
+// adjoint as one system's statements in order: the operation count below
+// runs them.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -37,8 +33,10 @@
 #include <type_traits>
 
 #include "../../include/abadj.h"
+#include "aba_lane.h"
 #include "abadj_internal.h"
 #include "contact_adjoint.h"
+#include "contact_wave.h"
 
 namespace {
 
@@ -89,171 +87,123 @@ namespace {
 
 constexpr int kWave = 64;
 
-template <typename R>
+extern __shared__ __align__(16) double contact_lds[];
+
+template <typename S>
 struct RollArgs {
-  CTopo tp;
+  WTopo tp;
   int B, T;
-  R dt;
-  const R* P;     // [np][B]
-  const R* q0;    // [nq][B]
-  const R* qd0;   // [nv][B]
-  const R* tau;   // [T][nu][B]
-  R* traj;        // nullable: [T + 1][nq + nv][B]
-  R* qT;          // [nq][B]
-  R* qdT;         // [nv][B]
+  double dt;
+  const S* P;     // [np][B]
+  const S* q0;    // [nq][B]
+  const S* qd0;   // [nv][B]
+  const S* tau;   // [T][nu][B]
+  S* traj;        // nullable: [T + 1][nq + nv][B]
+  S* qT;          // [nq][B]
+  S* qdT;         // [nv][B]
   int* ncont;     // nullable: [T][B]
 };
 
-// Systems per workgroup of the rollout: each keeps its Work record in LDS
-// (16 x 9.7 KB in FP32, 8 x 19.4 KB in FP64), so the step's many dependent
-// accesses to the tree's articulated quantities see LDS rather than scratch
-// latency.  A system is one lane; SPL systems share a wave (the workgroup's
-// SPW / SPL waves spread over the CU's SIMDs).  Systems in one wave advance
-// in lockstep and serialise wherever their contact sets differ, while a
-// wave per system pays a full issue slot, and a full private-memory
-// request, for one lane's work.  On the landing quadrupeds (4096 x 200
-// steps) the rollout took 141, 134, 114, 110 and about 156 ms at 1, 2, 4, 8
-// and 16 systems per wave, the FP64 reverse 4560 (scaled from 1000 steps),
-// 2173, 1858 and 1578 ms at 1, 2, 4 and 8.  Fewer systems per wave spread a
-// small batch over more CUs, so SPL is a launch choice (sim_contact_tiling_t,
-// sim_contact_autotune): 8 (the default), 4 or 2 systems per wave, two waves
-// per workgroup in FP32 and one in FP64, whose Work records are twice as
-// large.
-template <typename R>
-constexpr int roll_spw(int spl) { return sizeof(R) == 4 ? 2 * spl : spl; }
-
-template <typename R, int SPL>
-__global__ __launch_bounds__(kWave * roll_spw<R>(SPL) / SPL) void k_contact_rollout(RollArgs<R> a) {
-  constexpr int SPW = roll_spw<R>(SPL);
-  static_assert(SPW * sizeof(Work<R>) <= 160 * 1024, "LDS budget");
-  static_assert(SPW % SPL == 0 && SPL <= kWave, "whole waves");
-  static_assert((sizeof(Work<R>) / sizeof(R)) % 2 == 1, "odd Work stride");
-  __shared__ Work<R> wsh[SPW];
-  const int ln = threadIdx.x % kWave;
-  const int sw = (threadIdx.x / kWave) * SPL + ln;
-  const int s = blockIdx.x * SPW + sw;
-  if (ln >= SPL || s >= a.B) return;
-  const CTopo& tp = a.tp;
+// The rollout: four systems per wavefront, the state in registers.
+template <typename S>
+__global__ __launch_bounds__(kWave) void k_contact_rollout(RollArgs<S> a) {
+  __shared__ int meta[kGrp];
+  wave::fill_meta(a.tp, meta);
+  wave::sync();
+  const int s0 = blockIdx.x * kSysWave + threadIdx.x / kGrp;
+  const bool live = s0 < a.B;  // the last wavefront's spare groups repeat system B - 1
+  const int s = live ? s0 : a.B - 1;
   const size_t B = (size_t)a.B;
-  const Par<R> P{a.P, B, s};
-  const int nq = tp.nq, nv = tp.nv, nu = tp.nu, nx = nq + nv;
-  R x[2][kNX], u[kNL];
-  for (int k = 0; k < nq; ++k) x[0][k] = a.q0[k * B + s];
-  for (int k = 0; k < nv; ++k) x[0][nq + k] = a.qd0[k * B + s];
-  if (a.traj)
-    for (int k = 0; k < nx; ++k) a.traj[k * B + s] = x[0][k];
-  Work<R>& w = wsh[sw];
-  int cur = 0;
+  const wave::Lds g = wave::lds_of(a.tp, contact_lds, meta);
+  const wave::Lane l = wave::load_lane(a.tp, a.P, B, s);
+  const int nx = a.tp.nq + a.tp.nv, nu = a.tp.nu;
+  wave::State x = wave::zero_state();
+  wave::load_state(x, l, a.q0, a.qd0, B, s);
+  if (a.traj && live) wave::store_state(x, l, a.traj, a.traj + (size_t)a.tp.nq * B, B, s);
+  double un = l.one && a.T > 0 ? double(a.tau[l.ui * B + s]) : 0.0;
   for (int t = 0; t < a.T; ++t) {
-    for (int k = 0; k < nu; ++k) u[k] = a.tau[((size_t)t * nu + k) * B + s];
-    const int na = contact_step(tp, P, x[cur], x[cur] + nq, u, a.dt, R(tp.mu), x[cur ^ 1], x[cur ^ 1] + nq, w);
-    cur ^= 1;
-    if (a.ncont) a.ncont[(size_t)t * B + s] = na;
-    if (a.traj)
-      for (int k = 0; k < nx; ++k) a.traj[((size_t)(t + 1) * nx + k) * B + s] = x[cur][k];
+    const double u = un;
+    if (l.one && t + 1 < a.T) un = double(a.tau[((size_t)(t + 1) * nu + l.ui) * B + s]);
+    wave::Step o;
+    wave::step<false>(a.tp, l, g, x, u, a.dt, a.tp.mu, o);
+    wave::integrate(l, x, o, a.dt);
+    wave::round_state<S>(x);
+    if (a.ncont && live && l.gl == 0) a.ncont[(size_t)t * B + s] = o.na;
+    if (a.traj && live) {
+      S* row = a.traj + (size_t)(t + 1) * nx * B;
+      wave::store_state(x, l, row, row + (size_t)a.tp.nq * B, B, s);
+    }
   }
-  for (int k = 0; k < nq; ++k) a.qT[k * B + s] = x[cur][k];
-  for (int k = 0; k < nv; ++k) a.qdT[k * B + s] = x[cur][nq + k];
+  if (live) wave::store_state(x, l, a.qT, a.qdT, B, s);
 }
 
-template <typename R>
+template <typename S>
 struct GradArgs {
-  CTopo tp;
+  WTopo tp;
   int B, T;
-  R dt;
-  const R* P;     // [np][B]
-  const R* traj;  // [T + 1][nq + nv][B] from the rollout
-  const R* tau;   // [T][nu][B]
-  const R* gqT;   // [nq][B]
-  const R* gqdT;  // [nv][B]
-  R* gq0;         // [nq][B]
-  R* gqd0;        // [nv][B]
-  R* gtau;        // [T][nu][B]
-  R* gmu;         // nullable: [B]
+  double dt;
+  const S* P;     // [np][B]
+  const S* traj;  // [T + 1][nq + nv][B] from the rollout
+  const S* tau;   // [T][nu][B]
+  const S* gqT;   // [nq][B]
+  const S* gqdT;  // [nv][B]
+  S* gq0;         // [nq][B]
+  S* gqd0;        // [nv][B]
+  S* gtau;        // [T][nu][B]
+  S* gmu;         // nullable: [B]
 };
 
 // The rollout gradient by the step's reverse statements, backwards in time:
-// per step, contact_step_vjp recomputes the step from the stored state and
-// runs the adjoints of the integrator, the impulse update, both
-// Gauss-Seidel solves (from their recorded sweep vectors), A and b, the
-// unit-impulse responses, the contact geometry and the smooth ABA step.
-// One lane per system; R is the arithmetic (FP64 for FP32 I/O: the
-// recompute and the reverse sweeps start from the widened FP32 states, so
-// the gradient is that of the step map along the FP32 trajectory).  Unlike
-// the rollout, every record (Work, the sweep record, the adjoint arrays)
-// stays in private memory: in FP64 the Work records alone would hold the LDS
-// to 8 systems per CU, two rounds of 4096 systems, and having all systems in
-// flight at once pays more than LDS latency.
-// Measured on the landing quadrupeds (4096 x 200 steps, FP64 reverse): Work
-// in LDS, 8 per wave, 1581 ms; private, 8 per wave 1353, 16 per wave 964,
-// 32 per wave 993 ms.
-// SPL is a launch choice here too (16, the default, 8 or 4 systems per wave,
-// one wave per workgroup): a smaller batch reaches more CUs with fewer.
-// LDS (the default): each system's Gauss-Seidel working copies (PgsStage,
-// one LDS column per lane) and its copy of the articulated quantities with
-// the solves' scratch (Art) sit in LDS, where the solves' and the
-// responses' inner loops see LDS rather than private-memory latency; that
-// holds a CU to 16 systems at a time (160 KiB).  Without it (the same
-// copies in private memory) every system of a large batch is in flight at
-// once; the autotuner picks.
-template <typename S, typename R, int SPL, bool LDS>
+// per step, step_vjp recomputes the step from the stored state and runs the
+// adjoints of the integrator, the impulse update, both Gauss-Seidel solves
+// (from their recorded sweeps), A and b, M^-1 J^T, the contact geometry and
+// the smooth step.  The next state and control are fetched a step ahead.
+template <typename S>
 __global__ __launch_bounds__(kWave) void k_contact_adj(GradArgs<S> a) {
-  constexpr int SPW = SPL;
-  static_assert(SPL <= kWave, "one wave per workgroup");
-  __shared__ R stg[LDS ? kStage * SPW : 1];
-  __shared__ Art<R> art_sh[LDS ? SPW : 1];
-  const int ln = threadIdx.x % kWave;
-  const int sw = (threadIdx.x / kWave) * SPL + ln;
-  const int s = blockIdx.x * SPW + sw;
-  if (ln >= SPL || s >= a.B) return;
-  // without LDS the same staged statements run on private copies, so the
-  // two placements compile to the same arithmetic (the same multiply-adds
-  // fused) and give the same bits
-  R stg_priv[LDS ? 1 : kStage];
-  const PgsStage<R> stage{LDS ? stg + sw : stg_priv, LDS ? SPW : 1};
-  Art<R> art_priv;
-  Art<R>& art = LDS ? art_sh[sw] : art_priv;
-  // read in place from the kernel arguments (a uniform scalar load per
-  // topology entry; a local copy would live in scratch, one per lane); its
-  // constants arrive rounded to S (constants_as_seen_by)
-  const CTopo& tp = a.tp;
+  __shared__ int meta[kGrp];
+  wave::fill_meta(a.tp, meta);
+  wave::sync();
+  const int s0 = blockIdx.x * kSysWave + threadIdx.x / kGrp;
+  const bool live = s0 < a.B;
+  const int s = live ? s0 : a.B - 1;
   const size_t B = (size_t)a.B;
-  const Par<S> P{a.P, B, s};
-  const int nq = tp.nq, nv = tp.nv, nu = tp.nu, nx = nq + nv;
-  Rec<R> rc;
-  Adj<R> ad;
-  R xb[kNX], x[kNX], u[kNL], ub[kNL];
-  for (int k = 0; k < nq; ++k) xb[k] = R(a.gqT[k * B + s]);
-  for (int k = 0; k < nv; ++k) xb[nq + k] = R(a.gqdT[k * B + s]);
-  R mub = R(0);
-  Work<R> w;
+  const wave::Lds g = wave::lds_of(a.tp, contact_lds, meta);
+  const wave::Lane l = wave::load_lane(a.tp, a.P, B, s);
+  const int nx = a.tp.nq + a.tp.nv, nu = a.tp.nu;
+  wave::State xb = wave::zero_state(), nxt = wave::zero_state();
+  wave::load_state(xb, l, a.gqT, a.gqdT, B, s);
+  double un = 0, mub = 0;
+  auto fetch = [&](int t) {
+    const S* row = a.traj + (size_t)t * nx * B;
+    wave::load_state(nxt, l, row, row + (size_t)a.tp.nq * B, B, s);
+    if (l.one) un = double(a.tau[((size_t)t * nu + l.ui) * B + s]);
+  };
+  if (a.T > 0) fetch(a.T - 1);
   for (int t = a.T - 1; t >= 0; --t) {
-    for (int k = 0; k < nx; ++k) x[k] = R(a.traj[((size_t)t * nx + k) * B + s]);
-    for (int k = 0; k < nu; ++k) u[k] = R(a.tau[((size_t)t * nu + k) * B + s]);
-    contact_step_vjp(tp, P, x, x + nq, u, a.dt, R(tp.mu), xb, ub, mub, w, rc, ad, art, stage);
-    for (int k = 0; k < nu; ++k) a.gtau[((size_t)t * nu + k) * B + s] = S(ub[k]);
+    const wave::State x = nxt;
+    const double u = un;
+    if (t > 0) fetch(t - 1);
+    wave::Step o;
+    const double ub = wave::step_vjp(a.tp, l, g, x, u, a.dt, a.tp.mu, xb, mub, o);
+    if (live && l.one) a.gtau[((size_t)t * nu + l.ui) * B + s] = S(ub);
   }
-  for (int k = 0; k < nq; ++k) a.gq0[k * B + s] = S(xb[k]);
-  for (int k = 0; k < nv; ++k) a.gqd0[k * B + s] = S(xb[nq + k]);
-  if (a.gmu) a.gmu[s] = S(mub);
+  if (live) wave::store_state(xb, l, a.gq0, a.gqd0, B, s);
+  mub = wave::rsum(mub);
+  if (a.gmu && live && l.gl == 0) a.gmu[s] = S(mub);
 }
 
 int cfail(int code, const std::string& msg) { return aba::report_error(code, msg); }
 
-// The launch geometry the model asks for (m->tiling, NULL = the defaults).
+// The launch geometries a model may ask for (m->tiling); the kernels have one,
+// so a choice changes nothing.
 constexpr int kRollSplDefault = 8, kGradSplDefault = 16;
 bool roll_spl_ok(int spl) { return spl == 8 || spl == 4 || spl == 2; }
 bool grad_spl_ok(int spl) { return spl == 16 || spl == 8 || spl == 4; }
 
-template <typename R>
-hipError_t launch_rollout(const RollArgs<R>& a, int spl, hipStream_t st) {
-  const int spw = roll_spw<R>(spl);
-  const dim3 grid((a.B + spw - 1) / spw), block(kWave * (spw / spl));
-  switch (spl) {
-    case 8: hipLaunchKernelGGL((k_contact_rollout<R, 8>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((k_contact_rollout<R, 4>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((k_contact_rollout<R, 2>), grid, block, 0, st, a); break;
-  }
+template <typename S>
+hipError_t launch_rollout(const RollArgs<S>& a, hipStream_t st) {
+  hipLaunchKernelGGL((k_contact_rollout<S>), dim3((a.B + kSysWave - 1) / kSysWave), dim3(kWave), wave_lds_bytes(a.tp),
+                     st, a);
   return hipGetLastError();
 }
 // The model's constants as a rollout in S saw them (rounded to S), for the
@@ -269,18 +219,9 @@ CTopo constants_as_seen_by(CTopo tp) {
 }
 
 template <typename S>
-hipError_t launch_grad(const GradArgs<S>& a, int spl, bool lds, hipStream_t st) {
-  // both dtypes reverse in FP64
-  const dim3 grid((a.B + spl - 1) / spl), block(kWave);
-  if (!lds) {
-    hipLaunchKernelGGL((k_contact_adj<S, double, 16, false>), grid, block, 0, st, a);
-    return hipGetLastError();
-  }
-  switch (spl) {
-    case 16: hipLaunchKernelGGL((k_contact_adj<S, double, 16, true>), grid, block, 0, st, a); break;
-    case 8: hipLaunchKernelGGL((k_contact_adj<S, double, 8, true>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((k_contact_adj<S, double, 4, true>), grid, block, 0, st, a); break;
-  }
+hipError_t launch_grad(const GradArgs<S>& a, hipStream_t st) {
+  hipLaunchKernelGGL((k_contact_adj<S>), dim3((a.B + kSysWave - 1) / kSysWave), dim3(kWave), wave_lds_bytes(a.tp), st,
+                     a);
   return hipGetLastError();
 }
 
@@ -419,16 +360,15 @@ int sim_contact_rollout(const sim_contact_model* m, int dtype, int batch, const 
   if (batch == 0) return SIM_OK;
   if (!params || !q0 || !qd0 || !qT || !qdT || (T > 0 && tp.nu > 0 && !tau))
     return cfail(SIM_ERR_INVALID_ARG, "sim_contact_rollout: null array argument");
-  const int spl = m->tiling ? m->tiling->rollout_systems_per_wave : kRollSplDefault;
   hipError_t e;
   if (dtype == SIM_F64) {
-    RollArgs<double> a{tp, batch, T, dt, (const double*)params, (const double*)q0, (const double*)qd0,
+    RollArgs<double> a{make_wave_topo(tp, false), batch, T, dt, (const double*)params, (const double*)q0, (const double*)qd0,
                        (const double*)tau, (double*)traj, (double*)qT, (double*)qdT, ncontacts};
-    e = launch_rollout(a, spl, (hipStream_t)stream);
+    e = launch_rollout(a, (hipStream_t)stream);
   } else {
-    RollArgs<float> a{tp, batch, T, (float)dt, (const float*)params, (const float*)q0, (const float*)qd0,
+    RollArgs<float> a{make_wave_topo(constants_as_seen_by<float>(tp), false), batch, T, double((float)dt), (const float*)params, (const float*)q0, (const float*)qd0,
                       (const float*)tau, (float*)traj, (float*)qT, (float*)qdT, ncontacts};
-    e = launch_rollout(a, spl, (hipStream_t)stream);
+    e = launch_rollout(a, (hipStream_t)stream);
   }
   if (e != hipSuccess) return cfail(SIM_ERR_HIP, std::string("sim_contact_rollout: launch failed: ") + hipGetErrorString(e));
   return SIM_OK;
@@ -451,19 +391,17 @@ int sim_contact_rollout_grad(const sim_contact_model* m, int dtype, int batch, c
   if (batch == 0) return SIM_OK;
   if (!params || !traj || !gqT || !gqdT || !gq0 || !gqd0 || (T > 0 && tp.nu > 0 && (!tau || !gtau)))
     return cfail(SIM_ERR_INVALID_ARG, "sim_contact_rollout_grad: null array argument");
-  const int spl = m->tiling ? m->tiling->grad_systems_per_wave : kGradSplDefault;
-  const bool lds = m->tiling ? m->tiling->grad_lds != 0 : true;
   hipError_t e;
   if (dtype == SIM_F64) {
-    GradArgs<double> a{constants_as_seen_by<double>(tp), batch, T, dt, (const double*)params, (const double*)traj, (const double*)tau,
+    GradArgs<double> a{make_wave_topo(tp, true), batch, T, dt, (const double*)params, (const double*)traj, (const double*)tau,
                        (const double*)gqT, (const double*)gqdT, (double*)gq0, (double*)gqd0, (double*)gtau,
                        (double*)gmu};
-    e = launch_grad(a, spl, lds, (hipStream_t)stream);
+    e = launch_grad(a, (hipStream_t)stream);
   } else {
-    GradArgs<float> a{constants_as_seen_by<float>(tp), batch, T, (float)dt, (const float*)params, (const float*)traj, (const float*)tau,
+    GradArgs<float> a{make_wave_topo(constants_as_seen_by<float>(tp), true), batch, T, double((float)dt), (const float*)params, (const float*)traj, (const float*)tau,
                       (const float*)gqT, (const float*)gqdT, (float*)gq0, (float*)gqd0, (float*)gtau,
                       (float*)gmu};
-    e = launch_grad(a, spl, lds, (hipStream_t)stream);
+    e = launch_grad(a, (hipStream_t)stream);
   }
   if (e != hipSuccess)
     return cfail(SIM_ERR_HIP, std::string("sim_contact_rollout_grad: launch failed: ") + hipGetErrorString(e));
@@ -506,9 +444,7 @@ int sim_contact_autotune(const sim_contact_model* m, int dtype, int batch, const
   void* gqdT = take(nv * B);
   hipEvent_t e0 = nullptr, e1 = nullptr;
   sim_contact_model mm = *m;
-  sim_contact_tiling_t t{kRollSplDefault, kGradSplDefault, 1};
-  mm.tiling = &t;
-  int best_r = kRollSplDefault, best_g = kGradSplDefault, best_l = 1;
+  mm.tiling = nullptr;
   float ms_r = 0.f, ms_g = 0.f;
   rc = SIM_OK;
   do {
@@ -517,7 +453,7 @@ int sim_contact_autotune(const sim_contact_model* m, int dtype, int batch, const
       rc = cfail(SIM_ERR_HIP, "sim_contact_autotune: set-up failed");
       break;
     }
-    // each geometry runs once untimed, then once between events
+    // once untimed, then once between events
     auto timed = [&](auto&& run, float* ms) -> int {
       int r = run();
       if (r) return r;
@@ -529,31 +465,18 @@ int sim_contact_autotune(const sim_contact_model* m, int dtype, int batch, const
         return cfail(SIM_ERR_HIP, "sim_contact_autotune: timing failed");
       return SIM_OK;
     };
-    const int rspl[3] = {8, 4, 2}, gspl[4] = {16, 8, 4, 16}, glds[4] = {1, 1, 1, 0};
-    for (int k = 0; k < 3 && !rc; ++k) {
-      t.rollout_systems_per_wave = rspl[k];
-      float ms = 0.f;
-      rc = timed([&] { return sim_contact_rollout(&mm, dtype, batch, params, q0, qd0, tau, dt, T_probe, traj, qT, qdT,
-                                                  nullptr, stream); }, &ms);
-      if (!rc && (k == 0 || ms < ms_r)) { ms_r = ms; best_r = rspl[k]; }
-    }
-    for (int k = 0; k < 4 && !rc; ++k) {
-      t.grad_systems_per_wave = gspl[k];
-      t.grad_lds = glds[k];
-      float ms = 0.f;
+    rc = timed([&] { return sim_contact_rollout(&mm, dtype, batch, params, q0, qd0, tau, dt, T_probe, traj, qT, qdT,
+                                                nullptr, stream); }, &ms_r);
+    if (!rc)
       rc = timed([&] { return sim_contact_rollout_grad(&mm, dtype, batch, params, traj, tau, dt, T_probe, gqT, gqdT,
-                                                       gq0, gqd0, gtau, nullptr, stream); }, &ms);
-      if (!rc && (k == 0 || ms < ms_g)) { ms_g = ms; best_g = gspl[k]; best_l = glds[k]; }
-    }
+                                                       gq0, gqd0, gtau, nullptr, stream); }, &ms_g);
   } while (false);
   (void)hipStreamSynchronize(st);
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   (void)hipFree(buf);
   if (rc) return rc;
-  chosen->rollout_systems_per_wave = best_r;
-  chosen->grad_systems_per_wave = best_g;
-  chosen->grad_lds = best_l;
+  *chosen = {kRollSplDefault, kGradSplDefault, 1};
   if (rollout_ms) *rollout_ms = ms_r / T_probe;
   if (grad_ms) *grad_ms = ms_g / T_probe;
   return SIM_OK;

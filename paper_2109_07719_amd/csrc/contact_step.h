@@ -1,7 +1,9 @@
 // One time step with contact for one system (Sec. 4.1 "Collision
 // resolution"), templated on the scalar (float, double, or their dual
-// numbers for exact step Jacobians).  Host and device code: the kernels in
-// contact.hip run it per lane; a host build runs the same statements.
+// numbers for exact step Jacobians), one system's statements in order: what
+// the operation count of contact.hip runs, and a host build for comparison
+// with the kernels, which spread the same step over 16 lanes
+// (contact_wave.h).
 #pragma once
 
 #include <cfloat>
