@@ -431,6 +431,25 @@ int sim_pgs_adjoint(int dtype, int batch, int n, int niter, const void *A, const
                     size_t workspace_bytes, void *Abar, void *bbar, void *lobar, void *hibar,
                     void *x0bar, void *stream);
 
+/* ---- world positions of link points ----------------------------------------
+ * x[s] = world position of the point pts[s] (link coordinates) on the last
+ * link of path[s], from the joint coordinates q (the loss side of Sec. 3, Eq.
+ * diff_u); the adjoint writes dL/dq of <xbar, x> into the entries of gq that
+ * belong to the paths' joints (the caller clears gq: other entries keep their
+ * values).  All arrays are DEVICE arrays of the dtype, contiguous: path [n_sys]
+ * [len] int32 links (root first, -1 past the end, len <= SIM_MAX_LINKS, a free
+ * root only first), jtype [n_links] int32 (SIM_JOINT_*), qidx [n_links] int64
+ * (the joint's first entry of q), ETt [n_links][9] (E_T transposed), rT and ax
+ * [n_links][3] (the axis as given: no normalisation), pts, x, xbar [n_sys][3].
+ * Only enqueues work on `stream`.  Errors: SIM_ERR_INVALID_ARG,
+ * SIM_ERR_UNSUPPORTED_DTYPE, SIM_ERR_HIP. */
+int sim_link_points(int dtype, int n_sys, int len, const int32_t *path, const int32_t *jtype, const int64_t *qidx,
+                    const void *ETt, const void *rT, const void *ax, const void *pts, const void *q, void *x,
+                    void *stream);
+int sim_link_points_adjoint(int dtype, int n_sys, int len, const int32_t *path, const int32_t *jtype,
+                            const int64_t *qidx, const void *ETt, const void *rT, const void *ax, const void *pts,
+                            const void *q, const void *xbar, void *gq, void *stream);
+
 /* ---- contact inside the step ----------------------------------------------
  * Rollouts with collision detection and contact resolution between the
  * dynamics and the integrator (Sec. 4.1 "Collision resolution": detection,

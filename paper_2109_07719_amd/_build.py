@@ -29,6 +29,7 @@ UNITS = [
     ("abadj_runtime.hip", []),
     ("pgs.hip", []),
     ("contact.hip", []),
+    ("fk.hip", []),
 ]
 SOURCES = [os.path.join(CSRC, u) for u, _ in UNITS]
 

@@ -25,7 +25,7 @@ SIM_JOINT_PRISMATIC = 2
 SIM_JOINT_SPHERICAL = 3
 SIM_MAX_LINKS = 64
 
-EXPORTED = ("sim_create", "sim_destroy", "sim_get_info", "sim_set_adjoint_dtype", "sim_status", "sim_get_tiling",
+EXPORTED = ("sim_link_points", "sim_link_points_adjoint", "sim_create", "sim_destroy", "sim_get_info", "sim_set_adjoint_dtype", "sim_status", "sim_get_tiling",
             "sim_set_tiling", "sim_autotune", "sim_autotune_cache_clear",
             "sim_workspace_bytes",
             "sim_checkpoint_schedule", "sim_forward", "sim_forward_jvp",
@@ -128,6 +128,10 @@ def lib():
         L.sim_contact_rollout_grad.restype = I
         L.sim_contact_autotune.argtypes = [P, I, I, P, P, P, P, D, I, P, P, ctypes.POINTER(D), ctypes.POINTER(D)]
         L.sim_contact_autotune.restype = I
+        L.sim_link_points.argtypes = [I, I, I, P, P, P, P, P, P, P, P, P, P]
+        L.sim_link_points.restype = I
+        L.sim_link_points_adjoint.argtypes = [I, I, I, P, P, P, P, P, P, P, P, P, P, P]
+        L.sim_link_points_adjoint.restype = I
         L.sim_last_error.argtypes = []
         L.sim_last_error.restype = ctypes.c_char_p
         _lib = L

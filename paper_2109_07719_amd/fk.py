@@ -10,11 +10,25 @@ E^T = E_T^T Rot(a, q), Rot the rotation by +q about a, origin at r_T;
 prismatic: E^T = E_T^T, origin at r_T + q E_T^T a; spherical: E^T =
 E_T^T R(quat), origin at r_T; free root: R(quat) and p).  Other joint types
 are rejected.
+
+On the GPU the positions and their adjoint come from one kernel each
+(`sim_link_points`), a point's path to the root composed by one wavefront;
+anything beyond a plain first-order call (CPU tensors, higher derivatives,
+forward mode, function transforms, tracing) runs the torch expressions.
 """
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
+import torch.autograd.forward_ad as fwad
+from torch.utils._python_dispatch import _get_current_dispatch_mode
+
+from . import _native as N
+
+_DT = {torch.float32: N.SIM_F32, torch.float64: N.SIM_F64}
+_MAX_PATH = 64   # one lane per link of a path
 
 
 def _skew(a):
@@ -30,6 +44,45 @@ def _quat_R(qt):
         torch.stack([w * w + x * x - y * y - z * z, 2 * (x * y - w * z), 2 * (x * z + w * y)], -1),
         torch.stack([2 * (x * y + w * z), w * w - x * x + y * y - z * z, 2 * (y * z - w * x)], -1),
         torch.stack([2 * (x * z - w * y), 2 * (y * z + w * x), w * w - x * x - y * y + z * z], -1)], -2)
+
+
+def _paths(target, parent, jtype, most=_MAX_PATH):
+    """Links from the root to each target [n, longest], -1 past the end; a
+    free link starts its path.  None where a path is too long or a target
+    does not exist."""
+    n = len(parent)
+    if ((target < -n) | (target >= n)).any():
+        return None
+    cur, rows = np.where(target < 0, target + n, target), []
+    while (cur >= 0).any():
+        if len(rows) == most:
+            return None
+        rows.append(cur)
+        up = np.where(cur >= 0, parent[cur], -1)
+        cur = np.where((cur >= 0) & (jtype[cur] == 1), -1, up)
+    up = np.stack(rows, axis=1)                      # target first
+    size = (up >= 0).sum(axis=1, keepdims=True)
+    k = size - 1 - np.arange(up.shape[1])[None]
+    return np.where(k >= 0, np.take_along_axis(up, np.maximum(k, 0), axis=1), -1).astype(np.int32)
+
+
+class _Points(torch.autograd.Function):
+    @staticmethod
+    def forward(ctx, q, fk):
+        ctx.fk = fk
+        ctx.save_for_backward(q, fk.ETt, fk.rT, fk.ax, fk.pts)
+        x = torch.empty_like(fk.pts)
+        fk._call("sim_link_points", q, fk.ETt, fk.rT, fk.ax, fk.pts, x)
+        return x
+
+    @staticmethod
+    def backward(ctx, g):
+        q, *tables = ctx.saved_tensors
+        if torch.is_grad_enabled():   # a graph of the gradient is wanted
+            return torch.autograd.grad(ctx.fk._positions(q), q, g, create_graph=True)[0], None
+        gq = torch.zeros_like(q)
+        ctx.fk._call("sim_link_points_adjoint", q, *tables, g.contiguous(), gq)
+        return gq, None
 
 
 class LinkPoints(torch.nn.Module):
@@ -81,7 +134,42 @@ class LinkPoints(torch.nn.Module):
         self.level_ball = [np.nonzero(self.jtype[np.nonzero(self.depth == d)[0]] == 3)[0]
                            for d in range(int(self.depth.max()) + 1)]
 
+        path = _paths(np.asarray(target), np.asarray(glob_par), self.jtype)
+        self._path = None
+        if path is not None and self.rT.is_cuda:
+            self._path = torch.tensor(path, device=device)
+            self._jtype = torch.tensor(self.jtype, dtype=torch.int32, device=device)
+            self._nq = int(qbase)
+
+    def _native(self, q):
+        """Whether a call on q is one the kernels take."""
+        if self._path is None or type(q) not in (torch.Tensor, torch.nn.Parameter) or q.dtype not in _DT:
+            return False
+        if torch.compiler.is_compiling() or torch.jit.is_tracing():
+            return False
+        if torch._C._functorch.peek_interpreter_stack() is not None or _get_current_dispatch_mode() is not None:
+            return False
+        if torch.is_autocast_enabled() or fwad.unpack_dual(q).tangent is not None:
+            return False
+        fits = lambda t, n: (type(t) is torch.Tensor and t.dtype == q.dtype and t.device == q.device
+                             and t.numel() == n and t.is_contiguous() and not t.requires_grad)
+        n = self.n_links
+        return (q.device == self._path.device and q.dim() == 1 and q.numel() >= self._nq and q.is_contiguous()
+                and fits(self.ETt, 9 * n) and fits(self.rT, 3 * n) and fits(self.ax, 3 * n)
+                and fits(self.pts, 3 * self._path.shape[0]) and self.pts.dim() == 2)
+
+    def _call(self, name, q, ETt, rT, ax, pts, *last):
+        p = lambda t: ctypes.c_void_p(t.data_ptr())
+        with torch.cuda.device(q.device):
+            stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+            N.check(getattr(N.lib(), name)(_DT[q.dtype], self._path.shape[0], self._path.shape[1], p(self._path),
+                                           p(self._jtype), p(self.qidx), p(ETt), p(rT), p(ax), p(pts), p(q),
+                                           *(p(t) for t in last), stream))
+
     def forward(self, q):
+        return _Points.apply(q, self) if self._native(q) else self._positions(q)
+
+    def _positions(self, q):
         n = self.n_links
         Rw = torch.zeros((n, 3, 3), dtype=q.dtype, device=q.device)
         pw = torch.zeros((n, 3), dtype=q.dtype, device=q.device)
