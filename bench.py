@@ -46,7 +46,8 @@ FP32_PEAK_TFLOPS = 157.3   # MI355X FP32 vector peak (dual-issue); 78.6 without 
 FP64_PEAK_TFLOPS = 78.6    # MI355X FP64 vector peak
 
 
-KERNEL_SOURCES = ("csrc/spatial.h", "csrc/aba_lane.h", "csrc/dual.h", "csrc/abadj_device.h", "csrc/abadj_kernels.hip",
+KERNEL_SOURCES = ("csrc/spatial.h", "csrc/aba_lane.h", "csrc/dual.h", "csrc/abadj_device.h", "csrc/planar.h",
+                  "csrc/planar_adjoint.h", "csrc/abadj_kernels.hip",
                   "csrc/abadj_kernels_bwd.hip", "csrc/abadj_kernels_bwd64.hip", "csrc/abadj_kernels_chain.hip",
                   "_build.py")
 

@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libabadj.so")
 CSRC = os.path.join(HERE, "csrc")
-HEADERS = [os.path.join(CSRC, n) for n in ("spatial.h", "aba_lane.h", "dual.h", "abadj_device.h",
+HEADERS = [os.path.join(CSRC, n) for n in ("spatial.h", "aba_lane.h", "dual.h", "abadj_device.h", "planar.h", "planar_adjoint.h",
                                            "abadj_internal.h")] + [os.path.join(ROOT, "include", "abadj.h")]
 
 HIPCC_FLAGS = [

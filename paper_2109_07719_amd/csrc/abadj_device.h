@@ -192,6 +192,13 @@ __device__ __forceinline__ V3<S> gravity(const Packed<S>& P) {
 __device__ __forceinline__ int wave_in_block() { return threadIdx.x / kWave; }
 __device__ __forceinline__ int wave_batch() { return blockIdx.x * (blockDim.x / kWave) + wave_in_block(); }
 
+// deepest level of a wave batch, in a scalar register: the level loops then
+// count in scalar registers instead of masking lanes off
+template <typename S>
+__device__ __forceinline__ int wave_maxd(const Packed<S>& P, int wb) {
+  return __builtin_amdgcn_readfirstlane(P.wmaxd[wb]);
+}
+
 // ---- exchange buffer [field][lane]
 template <typename S>
 __device__ __forceinline__ void put6(S* xb, int f0, int lane, const V6<S>& v) {
@@ -645,6 +652,16 @@ __device__ __forceinline__ void aba_wave_chain(const V3<S>& g, const Lane& l, co
   }
 }
 
+}  // namespace
+
+}  // namespace aba
+
+#include "planar.h"
+
+namespace aba {
+
+namespace {
+
 // One ABA evaluation for the whole wave (all three passes).  tau: the
 // lane's controls (load_ctl).  BALL: the variant that also takes ball joints.
 template <typename S, bool FREE, bool CHAIN, bool BALL = false>
@@ -769,6 +786,36 @@ __device__ __forceinline__ void integrate_lane(State<S, FREE>& st, const Lane& l
   }
 }
 
+// Whether the rollouts of a variant take the planar step.  A handle whose
+// reverse runs in FP32 (R) keeps the general one: its store-all forward does,
+// whose tape holds the general step's intermediates, and in FP32 two steps
+// that round differently show between its checkpointing schemes.
+template <int FR, bool CHAIN, typename R>
+constexpr bool kPlanarStep = CHAIN && FR == kFrIdentity && sizeof(R) == sizeof(double);
+
+// The constants a forward step reads, loaded once (inside the time loop a
+// store could alias them, and every step would wait for them).
+template <bool PLANAR, typename T, typename S>
+__device__ __forceinline__ auto step_const(const Packed<S>& P, const Lane& l, const LinkC<T>& L) {
+  if constexpr (PLANAR) return planar_const<T>(P, l);
+  else return L;
+}
+// One forward step of the lane's state under the control tau, as every
+// rollout and segment replay takes it; L: step_const's.
+template <int FR, bool CHAIN, bool PLANAR, typename T, typename S, bool FREE, typename LC>
+__device__ __forceinline__ void advance(const Packed<S>& P, const V3<T>& g, const Lane& l, const LC& L,
+                                        State<T, FREE>& st, const V3<T>& tau, T dt, int maxd, T* xb) {
+  constexpr bool BALL = FREE && FR == kFrBall;
+  if constexpr (PLANAR) {
+    const T qdd = planar_qdd<T>(g, L, st.q[0], st.qd[0], tau.x, maxd);
+    if (l.active()) integrate_joint(st.q[0], st.qd[0], qdd, dt);
+  } else {
+    Step<T> o;
+    aba_wave<T, FREE, CHAIN, BALL>(g, l, L, st, limit_tau<FR>(P, l, st, tau), maxd, xb, o);
+    if (l.active()) integrate_lane<T, FREE, BALL>(st, l, o, dt);
+  }
+}
+
 // ------------------------------------------------------------------ kernels
 
 template <typename S, bool FREE, int FR, bool CHAIN>
@@ -776,7 +823,7 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_aba(AbaArgs<S> A)
   S* xb = CHAIN ? nullptr : lds<S>() + wave_in_block() * (XB * kWave);
   const int wb = wave_batch();
   const Lane l = load_lane(A.P, wb);
-  const int maxd = A.P.wmaxd[wb];
+  const int maxd = wave_maxd(A.P, wb);
   // every lane slot holds valid constants, so load them unconditionally
   // (keeps the compile-time axis and frame constants visible to folding)
   constexpr bool BALL = FREE && FR == kFrBall;
@@ -788,7 +835,10 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_aba(AbaArgs<S> A)
     tau = load_ctl<BALL>(A.tau, l);
   }
   Step<S> o;
-  aba_wave<S, FREE, CHAIN, BALL>(gravity(A.P), l, L, st, limit_tau<FR>(A.P, l, st, tau), maxd, xb, o);
+  if constexpr (CHAIN && FR == kFrIdentity)
+    o.t.qdd = planar_qdd<S>(gravity(A.P), planar_const<S>(A.P, l), st.q[0], st.qd[0], tau.x, maxd);
+  else
+    aba_wave<S, FREE, CHAIN, BALL>(gravity(A.P), l, L, st, limit_tau<FR>(A.P, l, st, tau), maxd, xb, o);
   int nonfin = 0;
   if (l.onedof()) {
     A.qdd[l.vidx] = o.t.qdd;
@@ -816,16 +866,19 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_aba(AbaArgs<S> A)
 // Forward rollout.  MODE 0: plain; 1: store the initial state of every
 // K-th step; 2: store every step's initial state and intermediates
 // (store-all).  With a trajectory buffer, also write x^{t+1} for every step.
-template <typename S, bool FREE, int FR, bool CHAIN, int MODE>
+// R: the type of the handle's reverse passes (kPlanarStep).
+template <typename S, typename R, bool FREE, int FR, bool CHAIN, int MODE>
 __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_forward(FwdArgs<S> A) {
+  constexpr bool PLANAR = kPlanarStep<FR, CHAIN, R> && MODE != 2;
   S* xb = CHAIN ? nullptr : lds<S>() + wave_in_block() * (XB * kWave);
   const int wb = wave_batch();
   const Lane l = load_lane(A.P, wb);
-  const int maxd = A.P.wmaxd[wb];
+  const int maxd = wave_maxd(A.P, wb);
   const int ns = A.P.nslots;
   const int nu = A.P.nu;
   constexpr bool BALL = FREE && FR == kFrBall;
   const LinkC<S> L = load_linkc<S, FR>(A.P, l);
+  const auto SC = step_const<PLANAR>(A.P, l, L);
   State<S, FREE> st = {};
   if (l.active()) load_state(st, l, A.q0, A.qd0);
   V3<S> tau_next = (l.active() && A.T > 0) ? load_ctl<BALL>(A.tau, l) : zero3<S>();
@@ -838,16 +891,18 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_forward(FwdArgs<S
     }
     const V3<S> tau = tau_next;
     if (l.active() && t + 1 < A.T) tau_next = load_ctl<BALL>(A.tau + (size_t)(t + 1) * nu, l);
-    Step<S> o;
-    aba_wave<S, FREE, CHAIN, BALL>(gravity(A.P), l, L, st, limit_tau<FR>(A.P, l, st, tau), maxd, xb, o);
     if constexpr (MODE == 2) {
+      Step<S> o;
+      aba_wave<S, FREE, CHAIN, BALL>(gravity(A.P), l, L, st, limit_tau<FR>(A.P, l, st, tau), maxd, xb, o);
       if (l.active()) {
         S* row = A.ck + (size_t)t * (RW + (size_t)kTapeFields * ns);
         put_slot(st, row, ns, nf, l.slot, l.fidx);
         put_tape(o, row + RW, ns, l.slot);
+        integrate_lane<S, FREE, BALL>(st, l, o, A.dt);
       }
+    } else {
+      advance<FR, CHAIN, PLANAR>(A.P, gravity(A.P), l, SC, st, tau, A.dt, maxd, xb);
     }
-    if (l.active()) integrate_lane<S, FREE, BALL>(st, l, o, A.dt);
     if (A.traj != nullptr) {
       if (l.active()) {
         S* row = A.traj + (size_t)t * (A.P.nq + A.P.nv);
@@ -1160,7 +1215,7 @@ __attribute__((amdgpu_waves_per_eu((FREE || sizeof(R) > 4) ? 1 : 2))) void k_bac
   S* xb = CHAIN ? nullptr : reinterpret_cast<S*>(lds<R>() + wave_in_block() * (XB * kWave));
   const int wb = wave_batch();
   const Lane l = load_lane(A.P, wb);
-  const int maxd = A.P.wmaxd[wb];
+  const int maxd = wave_maxd(A.P, wb);
   const int ns = A.P.nslots;
   const int nu = A.P.nu;
   constexpr bool BALL = FREE && FR == kFrBall;
@@ -1169,6 +1224,8 @@ __attribute__((amdgpu_waves_per_eu((FREE || sizeof(R) > 4) ? 1 : 2))) void k_bac
   const int nf = A.P.nfree;
   const LinkC<S> L = load_linkc<S, FR>(A.P, l);
   const LinkC<R> LR = widen<R>(L);
+  constexpr bool PLANAR = kPlanarStep<FR, CHAIN, R>;
+  const auto SC = step_const<PLANAR>(A.P, l, L);
   int nonfin = 0;  // non-finite outputs
   ParamBar<R> pg;
   param_bar_zero(pg);
@@ -1217,9 +1274,7 @@ __attribute__((amdgpu_waves_per_eu((FREE || sizeof(R) > 4) ? 1 : 2))) void k_bac
       } else if (what == SCH_ADVANCE) {
         for (int j = 0; j < arg; ++j, ++tc) {
           const V3<S> tau = act ? load_ctl<BALL>(A.tau + (size_t)tc * nu, l) : zero3<S>();
-          Step<S> o;
-          aba_wave<S, FREE, CHAIN, BALL>(gravity(A.P), l, L, cur, limit_tau<FR>(A.P, l, cur, tau), maxd, xb, o);
-          if (act) integrate_lane<S, FREE, BALL>(cur, l, o, A.dt);
+          advance<FR, CHAIN, PLANAR>(A.P, gravity(A.P), l, SC, cur, tau, A.dt, maxd, xb);
         }
       } else if (what == SCH_TAKESHOT) {
         if (act) put_slot(cur, A.ck + (size_t)slot * RW, ns, nf, l.slot, l.fidx);
@@ -1243,12 +1298,8 @@ __attribute__((amdgpu_waves_per_eu((FREE || sizeof(R) > 4) ? 1 : 2))) void k_bac
       for (int j = 1; j < t1 - t0; ++j) {
         const V3<S> tau = tau_nxt;
         if (act && j + 1 < t1 - t0) tau_nxt = load_ctl<BALL>(A.tau + (size_t)(t0 + j) * nu, l);
-        Step<S> o;
-        aba_wave<S, FREE, CHAIN, BALL>(gravity(A.P), l, L, st, limit_tau<FR>(A.P, l, st, tau), maxd, xb, o);
-        if (act) {
-          integrate_lane<S, FREE, BALL>(st, l, o, A.dt);
-          put_slot(st, A.scratch + (size_t)j * RW, ns, nf, l.slot, l.fidx);
-        }
+        advance<FR, CHAIN, PLANAR>(A.P, gravity(A.P), l, SC, st, tau, A.dt, maxd, xb);
+        if (act) put_slot(st, A.scratch + (size_t)j * RW, ns, nf, l.slot, l.fidx);
       }
       State<S, FREE> nxt = {};
       if (act) get_slot(nxt, A.scratch + (size_t)(t1 - 1 - t0) * RW, ns, nf, l.slot, l.fidx);
@@ -1297,7 +1348,7 @@ __global__ __launch_bounds__(2 * kWave * kMaxPairsPerBlock) void k_backward_pipe
   R* const tbuf0 = base + (CHAIN ? 0 : 2 * XB * kWave);
   const int wb = blockIdx.x * (blockDim.x / (2 * kWave)) + pair;
   const Lane l = load_lane(A.P, wb);
-  const int maxd = A.P.wmaxd[wb];
+  const int maxd = wave_maxd(A.P, wb);
   const int ns = A.P.nslots;
   const int nu = A.P.nu;
   constexpr bool BALL = FREE && FR == kFrBall;
@@ -1359,6 +1410,16 @@ __global__ __launch_bounds__(2 * kWave * kMaxPairsPerBlock) void k_backward_pipe
   }
 }
 
+}  // namespace
+
+}  // namespace aba
+
+#include "planar_adjoint.h"
+
+namespace aba {
+
+namespace {
+
 // Forward-mode rollout: the same step as k_forward with every value carried
 // as a dual number (value, derivative along the given input direction), so
 // it returns x^T and d x^T = (dx^T/dx^0) dx^0 + sum_t (dx^T/du^t) du^t, and
@@ -1400,9 +1461,10 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_forward_jvp(JvpAr
   D* xb = CHAIN ? nullptr : lds<D>() + wave_in_block() * (XB * kWave);
   const int wb = wave_batch();
   const Lane l = load_lane(A.P, wb);
-  const int maxd = A.P.wmaxd[wb];
+  const int maxd = wave_maxd(A.P, wb);
   const int nu = A.P.nu;
-  const LinkC<D> L = dual_const(load_linkc<S, FR>(A.P, l));
+  constexpr bool PLANAR = CHAIN && FR == kFrIdentity;
+  const auto SC = step_const<PLANAR>(A.P, l, dual_const(load_linkc<S, FR>(A.P, l)));
   const V3<D> g = v3<D>(D(A.P.g[0], S(0)), D(A.P.g[1], S(0)), D(A.P.g[2], S(0)));
   const D dt = D(A.dt, S(0));
   State<S, FREE> sv = {}, sd = {};
@@ -1424,9 +1486,7 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_forward_jvp(JvpAr
       td = load_ctl<BALL>(A.dtau + (size_t)t * nu, l);
     }
     const V3<D> tau = v3<D>(D(tv.x, td.x), D(tv.y, td.y), D(tv.z, td.z));
-    Step<D> o;
-    aba_wave<D, FREE, CHAIN, BALL>(g, l, L, st, limit_tau<FR>(A.P, l, st, tau), maxd, xb, o);
-    if (l.active()) integrate_lane<D, FREE, BALL>(st, l, o, dt);
+    advance<FR, CHAIN, PLANAR>(A.P, g, l, SC, st, tau, dt, maxd, xb);
     if (A.traj != nullptr && l.active()) {
       split_state(st, sv, sd);
       S* row = A.traj + (size_t)t * (A.P.nq + A.P.nv);
@@ -1479,33 +1539,90 @@ hipError_t launch_aba_v(const AbaArgs<S>& a, const Tiling& tl, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <typename S, bool F, int E, bool C>
-hipError_t launch_forward_v(const FwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
-  if (a.P.nwaves == 0) return hipSuccess;
+template <typename S, typename R, bool F, int E, bool C>
+hipError_t launch_forward_r(const FwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
   const int mode = (a.ck == nullptr) ? 0 : (a.K == 0) ? 2 : 1;
   size_t lds = 0;
   const int w = single_wpb<S, C>(tl, a.P.nwaves, lds);
   const dim3 grid(a.P.nwaves / w), block(kWave * w);
-  if (mode == 0) hipLaunchKernelGGL((k_forward<S, F, E, C, 0>), grid, block, lds, st, a);
-  else if (mode == 1) hipLaunchKernelGGL((k_forward<S, F, E, C, 1>), grid, block, lds, st, a);
-  else hipLaunchKernelGGL((k_forward<S, F, E, C, 2>), grid, block, lds, st, a);
+  if (mode == 0) hipLaunchKernelGGL((k_forward<S, R, F, E, C, 0>), grid, block, lds, st, a);
+  else if (mode == 1) hipLaunchKernelGGL((k_forward<S, R, F, E, C, 1>), grid, block, lds, st, a);
+  else hipLaunchKernelGGL((k_forward<S, double, F, E, C, 2>), grid, block, lds, st, a);
+  return hipGetLastError();
+}
+template <typename S, bool F, int E, bool C>
+hipError_t launch_forward_v(const FwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
+  if (a.P.nwaves == 0) return hipSuccess;
+  if constexpr (kPlanarStep<E, C, double> && sizeof(S) == sizeof(float)) {
+    if (!a.adj64) return launch_forward_r<S, float, F, E, C>(a, tl, st);
+  }
+  return launch_forward_r<S, double, F, E, C>(a, tl, st);
+}
+
+// SIMDs of the current device.
+inline int simd_count() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 1024;
+  return 4 * cus;
+}
+
+template <typename S, int NP>
+hipError_t launch_planar_pipe(const BwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
+  const size_t per = planar_lds_per_group<NP>();
+  int p = tl.chosen && tl.pairs_per_block == 2 ? 2 : 1;
+  while (p > 1 && (per * p > lds_limit() || a.P.nwaves % p != 0)) p /= 2;
+  hipLaunchKernelGGL((k_backward_planar_pipe<S, NP>), dim3(a.P.nwaves / p), dim3((NP + 1) * kWave * p), per * p, st, a);
+  return hipGetLastError();
+}
+template <typename S>
+hipError_t launch_backward_planar(const BwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
+  // Unless the caller or the autotuner chose: pipelined, one batch per
+  // workgroup, up to one and a half batches per SIMD (chains of 7 links x 40
+  // steps, pipelined / one wavefront: 456 batches 95 / 182 us, 912 159 / 189,
+  // 1824 294 / 273, 7284 1028 / 971; two batches per workgroup are slower, 102
+  // us at 456 and 391 at 1824)
+  const bool pipe = tl.chosen ? tl.pipelined : 2 * a.P.nwaves <= 3 * simd_count();
+  if (a.K == 1 && pipe) {
+    // a recompute takes about twice a reverse's instructions: two recomputing
+    // wavefronts keep one reversing one busy; a third helps while the chip
+    // holds few batches (4096 chains of 7 links, 456 batches x 200 steps: 614,
+    // 454 and 420 us with one, two and three; 2048 chains of 5 to 50 links,
+    // 1216 batches x 50 steps: 807, 716 and 843 us)
+    if (2 * a.P.nwaves <= simd_count()) return launch_planar_pipe<S, 3>(a, tl, st);
+    return launch_planar_pipe<S, 2>(a, tl, st);
+  }
+  size_t lds = 0;
+  const int w = single_wpb<double, true>(tl, a.P.nwaves, lds);
+  hipLaunchKernelGGL((k_backward_planar<S>), dim3(a.P.nwaves / w), dim3(kWave * w), lds, st, a);
+  return hipGetLastError();
+}
+
+template <typename S, typename R, bool F, int E, bool C, bool PARAMS>
+hipError_t launch_backward_one(const BwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
+  size_t lds = 0;
+  const int w = single_wpb<R, C>(tl, a.P.nwaves, lds);
+  hipLaunchKernelGGL((k_backward<S, R, F, E, C, PARAMS>), dim3(a.P.nwaves / w), dim3(kWave * w), lds, st, a);
   return hipGetLastError();
 }
 
 template <typename S, typename R, bool F, int E, bool C, bool PARAMS>
 hipError_t launch_backward_p(const BwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
-  if (a.K == 1 && tl.pipelined) {
+  // planar chains; the model-parameter gradients, the stored intermediates
+  // (K == 0) and the FP32 reverse stay with the general kernels
+  if constexpr (C && E == kFrIdentity && !PARAMS && sizeof(R) == sizeof(double)) {
+    if (a.K != 0) return launch_backward_planar(a, tl, st);
+    return launch_backward_one<S, R, F, E, C, PARAMS>(a, tl, st);
+  } else if (a.K == 1 && tl.pipelined) {
     const size_t per = pipe_lds_per_pair<S, R, F, E, C>();
     int p = tl.pairs_per_block == 2 ? 2 : 1;
     while (p > 1 && (per * p > lds_limit() || a.P.nwaves % p != 0)) p /= 2;
     hipLaunchKernelGGL((k_backward_pipe<S, R, F, E, C, PARAMS>), dim3(a.P.nwaves / p), dim3(2 * kWave * p),
                        per * p, st, a);
-  } else {
-    size_t lds = 0;
-    const int w = single_wpb<R, C>(tl, a.P.nwaves, lds);
-    hipLaunchKernelGGL((k_backward<S, R, F, E, C, PARAMS>), dim3(a.P.nwaves / w), dim3(kWave * w), lds, st, a);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  return launch_backward_one<S, R, F, E, C, PARAMS>(a, tl, st);
 }
 // the kernels that accumulate model-parameter gradients only when asked for;
 // R: the reverse passes' scalar type

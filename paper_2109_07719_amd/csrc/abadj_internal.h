@@ -57,6 +57,7 @@ struct FwdArgs {
   S* ck;         // nullable: K >= 1 checkpoints [ceil(T/K)][state width][nslots];
                  // K == 0 every step's state and intermediates
                  // [T][state width + kTapeFields][nslots]
+  int adj64 = 1; // S = float: the handle's reverse passes run in FP64
 };
 
 template <typename S>
@@ -150,6 +151,7 @@ struct Tiling {
   int waves_per_block = 1;
   int pairs_per_block = 1;
   bool pipelined = true;
+  bool chosen = false;  // by the caller or the autotuner (a kernel's own rule yields to it)
 };
 
 // Link-frame kinds of a kernel variant.  kFrIdentity: every E_T the

@@ -670,6 +670,7 @@ int sim_set_tiling(sim_t h, const sim_tiling_t* t) {
   h->tiling.waves_per_block = w;
   h->tiling.pairs_per_block = p;
   h->tiling.pipelined = t->pipelined != 0;
+  h->tiling.chosen = true;
   return SIM_OK;
 }
 
@@ -785,6 +786,7 @@ int sim_forward(sim_t h, const void* q0, const void* qd0, const void* tau, doubl
     a.qdT = (float*)qdT;
     a.traj = (float*)traj;
     a.ck = (float*)workspace;
+    a.adj64 = h->adj_dtype == SIM_F64 ? 1 : 0;
     e = aba::launch_forward(a, shape(h), h->tiling, (hipStream_t)stream);
   }
   if (e != hipSuccess) return fail(SIM_ERR_HIP, std::string("sim_forward: launch failed: ") + hipGetErrorString(e));
@@ -1123,6 +1125,7 @@ int sim_autotune(sim_t h, int K, int T_probe, void* stream, sim_tiling_t* chosen
   const int wpbs[3] = {1, 2, 4};
   double F[3], Bnp[3], Bp[2] = {1e300, 1e300};
   ok = true;
+  h->tiling.chosen = true;
   for (int i = 0; ok && i < 3; ++i) {
     h->tiling.waves_per_block = wpbs[i];
     h->tiling.pipelined = false;
@@ -1142,6 +1145,7 @@ int sim_autotune(sim_t h, int K, int T_probe, void* stream, sim_tiling_t* chosen
   // forward and non-pipelined adjoint share waves_per_block
   double best = 1e300;
   aba::Tiling win;
+  win.chosen = true;
   for (int i = 0; i < 3; ++i) {
     for (int c = 0; c < 3; ++c) {  // c = 0: one-wave adjoint; 1, 2: pipelined with c pairs
       const double b = (c == 0) ? Bnp[i] : Bp[c - 1];
