@@ -47,7 +47,7 @@ FP64_PEAK_TFLOPS = 78.6    # MI355X FP64 vector peak
 
 
 KERNEL_SOURCES = ("csrc/spatial.h", "csrc/aba_lane.h", "csrc/dual.h", "csrc/abadj_device.h", "csrc/planar.h",
-                  "csrc/planar_adjoint.h", "csrc/abadj_kernels.hip",
+                  "csrc/planar_adjoint.h", "csrc/frame_adjoint.h", "csrc/abadj_kernels.hip",
                   "csrc/abadj_kernels_bwd.hip", "csrc/abadj_kernels_bwd64.hip", "csrc/abadj_kernels_chain.hip",
                   "_build.py")
 

@@ -9,7 +9,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libabadj.so")
 CSRC = os.path.join(HERE, "csrc")
 HEADERS = [os.path.join(CSRC, n) for n in ("spatial.h", "aba_lane.h", "dual.h", "abadj_device.h", "planar.h", "planar_adjoint.h",
-                                           "abadj_internal.h")] + [os.path.join(ROOT, "include", "abadj.h")]
+                                           "frame_adjoint.h", "abadj_internal.h")] + [os.path.join(ROOT, "include", "abadj.h")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC",

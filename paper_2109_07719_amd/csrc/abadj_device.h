@@ -31,7 +31,7 @@ namespace aba {
 
 namespace {
 
-constexpr int XB = 27;  // exchange-buffer fields per lane
+constexpr int XB = 28;  // numbers of a lane's exchange record
 
 // Synchronisation of the lanes of one wavefront around the LDS exchange
 // buffer: the wave executes its LDS operations in order, so a compiler
@@ -199,39 +199,75 @@ __device__ __forceinline__ int wave_maxd(const Packed<S>& P, int wb) {
   return __builtin_amdgcn_readfirstlane(P.wmaxd[wb]);
 }
 
-// ---- exchange buffer [field][lane]
-template <typename S>
-__device__ __forceinline__ void put6(S* xb, int f0, int lane, const V6<S>& v) {
-  xb[(f0 + 0) * kWave + lane] = v.a.x;
-  xb[(f0 + 1) * kWave + lane] = v.a.y;
-  xb[(f0 + 2) * kWave + lane] = v.a.z;
-  xb[(f0 + 3) * kWave + lane] = v.l.x;
-  xb[(f0 + 4) * kWave + lane] = v.l.y;
-  xb[(f0 + 5) * kWave + lane] = v.l.z;
+// ---- exchange buffer: a record of 28 numbers per lane
+// At one level of a tree few lanes are at work, so an exchange costs its
+// number of LDS instructions more than its bytes: a record moves 16 bytes at a
+// time (an inertia and a force in FP64: 14 instructions), where [field][lane]
+// would take one instruction per number.  The stride of 28 keeps consecutive
+// lanes' 16-byte pieces on distinct banks.  Adjoint of trees_8192's structures
+// in FP64, 50 steps: 1.83 -> 1.68 ms.
+template <typename S, int N>
+__device__ __forceinline__ void put_rec(S* xb, int lane, int at, const S (&v)[N]) {
+  constexpr int C = 16 / (int)sizeof(S);
+  struct alignas(16) Chunk { S v[C]; };
+  struct alignas(2 * sizeof(S) < 16 ? 2 * sizeof(S) : 16) Two { S v[2]; };
+  S* const p = xb + lane * XB + at;
+#pragma unroll
+  for (int k = 0; k + C <= N; k += C) {
+    Chunk c;
+#pragma unroll
+    for (int j = 0; j < C; ++j) c.v[j] = v[k + j];
+    *reinterpret_cast<Chunk*>(p + k) = c;
+  }
+  if constexpr (N % C == 2) *reinterpret_cast<Two*>(p + N - 2) = Two{{v[N - 2], v[N - 1]}};
+  static_assert(N % C == 0 || N % C == 2, "whole pieces");
+}
+template <typename S, int N>
+__device__ __forceinline__ void get_rec(const S* xb, int lane, int at, S (&v)[N]) {
+  constexpr int C = 16 / (int)sizeof(S);
+  struct alignas(16) Chunk { S v[C]; };
+  struct alignas(2 * sizeof(S) < 16 ? 2 * sizeof(S) : 16) Two { S v[2]; };
+  const S* const p = xb + lane * XB + at;
+#pragma unroll
+  for (int k = 0; k + C <= N; k += C) {
+    const Chunk c = *reinterpret_cast<const Chunk*>(p + k);
+#pragma unroll
+    for (int j = 0; j < C; ++j) v[k + j] = c.v[j];
+  }
+  if constexpr (N % C == 2) {
+    const Two c = *reinterpret_cast<const Two*>(p + N - 2);
+    v[N - 2] = c.v[0];
+    v[N - 1] = c.v[1];
+  }
 }
 template <typename S>
-__device__ __forceinline__ V6<S> get6(const S* xb, int f0, int lane) {
-  return v6<S>(v3<S>(xb[(f0 + 0) * kWave + lane], xb[(f0 + 1) * kWave + lane], xb[(f0 + 2) * kWave + lane]),
-               v3<S>(xb[(f0 + 3) * kWave + lane], xb[(f0 + 4) * kWave + lane], xb[(f0 + 5) * kWave + lane]));
+__device__ __forceinline__ void put6(S* xb, int at, int lane, const V6<S>& v) {
+  const S t[6] = {v.a.x, v.a.y, v.a.z, v.l.x, v.l.y, v.l.z};
+  put_rec(xb, lane, at, t);
 }
 template <typename S>
-__device__ __forceinline__ void put21(S* xb, int f0, int lane, const SySp<S>& M) {
-  const S v[21] = {M.A.xx, M.A.yy, M.A.zz, M.A.xy, M.A.xz, M.A.yz, M.B.m[0], M.B.m[1], M.B.m[2], M.B.m[3], M.B.m[4],
-                   M.B.m[5], M.B.m[6], M.B.m[7], M.B.m[8], M.C.xx, M.C.yy, M.C.zz, M.C.xy, M.C.xz, M.C.yz};
-#pragma unroll
-  for (int k = 0; k < 21; ++k) xb[(f0 + k) * kWave + lane] = v[k];
+__device__ __forceinline__ V6<S> get6(const S* xb, int at, int lane) {
+  S t[6];
+  get_rec(xb, lane, at, t);
+  return v6<S>(v3<S>(t[0], t[1], t[2]), v3<S>(t[3], t[4], t[5]));
+}
+// a symmetric inertia (21 numbers) and a force
+template <typename S>
+__device__ __forceinline__ void put27(S* xb, int lane, const SySp<S>& M, const V6<S>& f) {
+  const S t[28] = {M.A.xx,   M.A.yy,   M.A.zz,   M.A.xy,   M.A.xz,   M.A.yz, M.B.m[0], M.B.m[1], M.B.m[2], M.B.m[3],
+                   M.B.m[4], M.B.m[5], M.B.m[6], M.B.m[7], M.B.m[8], M.C.xx, M.C.yy,   M.C.zz,   M.C.xy,   M.C.xz,
+                   M.C.yz,   f.a.x,    f.a.y,    f.a.z,    f.l.x,    f.l.y,  f.l.z,    S(0)};
+  put_rec(xb, lane, 0, t);
 }
 template <typename S>
-__device__ __forceinline__ SySp<S> get21(const S* xb, int f0, int lane) {
-  S v[21];
+__device__ __forceinline__ void get27(const S* xb, int lane, SySp<S>& M, V6<S>& f) {
+  S t[28];
+  get_rec(xb, lane, 0, t);
+  M.A = sy3<S>(t[0], t[1], t[2], t[3], t[4], t[5]);
 #pragma unroll
-  for (int k = 0; k < 21; ++k) v[k] = xb[(f0 + k) * kWave + lane];
-  SySp<S> M;
-  M.A = sy3<S>(v[0], v[1], v[2], v[3], v[4], v[5]);
-#pragma unroll
-  for (int k = 0; k < 9; ++k) M.B.m[k] = v[6 + k];
-  M.C = sy3<S>(v[15], v[16], v[17], v[18], v[19], v[20]);
-  return M;
+  for (int k = 0; k < 9; ++k) M.B.m[k] = t[6 + k];
+  M.C = sy3<S>(t[15], t[16], t[17], t[18], t[19], t[20]);
+  f = v6<S>(v3<S>(t[21], t[22], t[23]), v3<S>(t[24], t[25], t[26]));
 }
 
 // per-lane state: 1-dof lanes use q[0], qd[0]; a free root uses
@@ -714,8 +750,11 @@ __device__ __forceinline__ void aba_wave(const V3<S>& g, const Lane& l, const Li
   for (int d = maxd; d >= 0; --d) {
     if (act && l.depth == d) {
       for (int k = 0; k < l.ccount; ++k) {
-        t.IA = t.IA + get21(xb, 0, l.cfirst + k);
-        t.pA = t.pA + get6(xb, 21, l.cfirst + k);
+        SySp<S> IAc;
+        V6<S> pAc;
+        get27(xb, l.cfirst + k, IAc, pAc);
+        t.IA = t.IA + IAc;
+        t.pA = t.pA + pAc;
       }
       if (rev) {
         p2_local(L, t, tau.x);
@@ -723,8 +762,7 @@ __device__ __forceinline__ void aba_wave(const V3<S>& g, const Lane& l, const Li
           SySp<S> IAu;
           V6<S> pAu;
           p2_push(L, t, IAu, pAu);
-          put21(xb, 0, l.lane, IAu);
-          put6(xb, 21, l.lane, pAu);
+          put27(xb, l.lane, IAu, pAu);
         }
       } else if (ball) {
         o.abase.l = ball_p2_local(t, tau);
@@ -732,8 +770,7 @@ __device__ __forceinline__ void aba_wave(const V3<S>& g, const Lane& l, const Li
           SySp<S> IAu;
           V6<S> pAu;
           ball_p2_push(L, t, tau, IAu, pAu);
-          put21(xb, 0, l.lane, IAu);
-          put6(xb, 21, l.lane, pAu);
+          put27(xb, l.lane, IAu, pAu);
         }
       }
     }
@@ -1040,13 +1077,13 @@ __device__ __forceinline__ void bwd_reverse(const BwdArgs<S>& A, const Lane& l, 
       if (act && l.depth == d) {
         if (rev || ball) {
           const bool hp = l.par >= 0;
-          const SySp<R> IAbp = hp ? get21(xb, 0, l.par) : zero_sysp<R>();
-          const V6<R> pAbp = hp ? get6(xb, 21, l.par) : zero6<R>();
+          SySp<R> IAbp = zero_sysp<R>();
+          V6<R> pAbp = zero6<R>();
+          if (hp) get27(xb, l.par, IAbp, pAbp);
           if (rev) taub = r2_path(L, tp, b, hp, IAbp, pAbp, N, pab, IAb, pAb);
           else btaub = ball_r2_path(L, tp, bb, o.abase.l, hp, IAbp, pAbp, N, pab, IAb, pAb);
         }
-        put21(xb, 0, l.lane, IAb);
-        put6(xb, 21, l.lane, pAb);
+        put27(xb, l.lane, IAb, pAb);
       }
       wave_sync();
     }
@@ -1197,6 +1234,16 @@ __device__ __forceinline__ int store_adjoint(const BwdArgs<S>& A, const Lane& l,
   return n;
 }
 
+}  // namespace
+
+}  // namespace aba
+
+#include "frame_adjoint.h"
+
+namespace aba {
+
+namespace {
+
 // Backward (adjoint) rollout, reverse time.  K == 1 reloads every step's
 // checkpoint; K > 1 replays each K-step segment from its checkpoint into
 // the scratch buffer first.  The next state and control are fetched one
@@ -1209,10 +1256,12 @@ __device__ __forceinline__ int store_adjoint(const BwdArgs<S>& A, const Lane& l,
 // PARAMS: the variant that also accumulates model-parameter gradients.
 // R: the scalar type of the reverse passes (see bwd_reverse); the exchange
 // buffer is sized for it.
-template <typename S, typename R, bool FREE, int FR, bool CHAIN, bool PARAMS>
+// FRAME: each step by the base-frame adjoint (frame_adjoint.h; R = double,
+// K != 0, no model-parameter gradients), whatever CHAIN.
+template <typename S, typename R, bool FREE, int FR, bool CHAIN, bool PARAMS, bool FRAME>
 __global__ __launch_bounds__(kWave * kMaxWavesPerBlock)
-__attribute__((amdgpu_waves_per_eu((FREE || sizeof(R) > 4) ? 1 : 2))) void k_backward(BwdArgs<S> A) {
-  S* xb = CHAIN ? nullptr : reinterpret_cast<S*>(lds<R>() + wave_in_block() * (XB * kWave));
+__attribute__((amdgpu_waves_per_eu(FRAME ? (FREE ? 1 : 2) : (FREE || sizeof(R) > 4) ? 1 : 2))) void k_backward(BwdArgs<S> A) {
+  S* xb = CHAIN && !FRAME ? nullptr : reinterpret_cast<S*>(lds<R>() + wave_in_block() * (XB * kWave));
   const int wb = wave_batch();
   const Lane l = load_lane(A.P, wb);
   const int maxd = wave_maxd(A.P, wb);
@@ -1230,7 +1279,15 @@ __attribute__((amdgpu_waves_per_eu((FREE || sizeof(R) > 4) ? 1 : 2))) void k_bac
   ParamBar<R> pg;
   param_bar_zero(pg);
   State<R, FREE> xb1 = seed_state<S, R, FREE>(A, l);
-  if (A.K == 0) {
+  const auto FL = [&] {
+    if constexpr (FRAME) return frame_lane<S, FR>(A.P, l, maxd);
+    else return 0;
+  }();
+  auto reverse = [&](const State<S, FREE>& st, const V3<S>& tau, int t) {
+    if constexpr (FRAME) frame_step<S, FREE, FR>(A, l, FL, reinterpret_cast<R*>(xb), st, tau, t, xb1, nonfin);
+    else bwd_step<S, R, FREE, FR, CHAIN, PARAMS>(A, l, LR, maxd, xb, st, tau, t, xb1, nonfin, pg);
+  };
+  if (!FRAME && A.K == 0) {
     // store-all: read every step's intermediates instead of recomputing
     for (int t = A.T - 1; t >= 0; --t) {
       State<S, FREE> st = {};
@@ -1241,8 +1298,9 @@ __attribute__((amdgpu_waves_per_eu((FREE || sizeof(R) > 4) ? 1 : 2))) void k_bac
         get_tape(o, row + RW, ns, l.slot, L, st.qd[0], l.onedof());
       }
       // the stored intermediates are the forward's (type S), widened
-      bwd_reverse<S, R, FREE, FR, CHAIN, PARAMS>(A, l, LR, maxd, reinterpret_cast<R*>(xb), cvt_state<R>(st),
-                                                 cvt_step<R>(o), t, xb1, nonfin, pg);
+      if constexpr (!FRAME)
+        bwd_reverse<S, R, FREE, FR, CHAIN, PARAMS>(A, l, LR, maxd, reinterpret_cast<R*>(xb), cvt_state<R>(st),
+                                                   cvt_step<R>(o), t, xb1, nonfin, pg);
     }
   } else if (A.K == 1) {
     State<S, FREE> nxt = {};
@@ -1258,7 +1316,7 @@ __attribute__((amdgpu_waves_per_eu((FREE || sizeof(R) > 4) ? 1 : 2))) void k_bac
         get_slot(nxt, A.ck + (size_t)(t - 1) * RW, ns, nf, l.slot, l.fidx);
         tau_nxt = load_ctl<BALL>(A.tau + (size_t)(t - 1) * nu, l);
       }
-      bwd_step<S, R, FREE, FR, CHAIN, PARAMS>(A, l, LR, maxd, xb, st, tau, t, xb1, nonfin, pg);
+      reverse(st, tau, t);
     }
   } else if (A.K < 0) {
     // binomial checkpointing: every wave runs the same host-built schedule
@@ -1280,7 +1338,7 @@ __attribute__((amdgpu_waves_per_eu((FREE || sizeof(R) > 4) ? 1 : 2))) void k_bac
         if (act) put_slot(cur, A.ck + (size_t)slot * RW, ns, nf, l.slot, l.fidx);
       } else {
         const V3<S> tau = act ? load_ctl<BALL>(A.tau + (size_t)arg * nu, l) : zero3<S>();
-        bwd_step<S, R, FREE, FR, CHAIN, PARAMS>(A, l, LR, maxd, xb, cur, tau, arg, xb1, nonfin, pg);
+        reverse(cur, tau, arg);
       }
     }
   } else {
@@ -1311,7 +1369,7 @@ __attribute__((amdgpu_waves_per_eu((FREE || sizeof(R) > 4) ? 1 : 2))) void k_bac
           get_slot(nxt, A.scratch + (size_t)(t - 1 - t0) * RW, ns, nf, l.slot, l.fidx);
           tau_nxt = load_ctl<BALL>(A.tau + (size_t)(t - 1) * nu, l);
         }
-        bwd_step<S, R, FREE, FR, CHAIN, PARAMS>(A, l, LR, maxd, xb, cur, tau, t, xb1, nonfin, pg);
+        reverse(cur, tau, t);
       }
     }
   }
@@ -1409,16 +1467,6 @@ __global__ __launch_bounds__(2 * kWave * kMaxPairsPerBlock) void k_backward_pipe
     report_nonfinite(A.P.status, nonfin);
   }
 }
-
-}  // namespace
-
-}  // namespace aba
-
-#include "planar_adjoint.h"
-
-namespace aba {
-
-namespace {
 
 // Forward-mode rollout: the same step as k_forward with every value carried
 // as a dual number (value, derivative along the given input direction), so
@@ -1518,10 +1566,14 @@ inline size_t lds_limit() {
 
 // waves per block of the single-wave kernels, reduced until the exchange
 // buffers fit (the wave count is a multiple of every power of two up to
-// kMaxWavesPerBlock)
+// kMaxWavesPerBlock).  Unless the caller or the autotuner chose: one, so that
+// few waves spread over the CUs (FP64 adjoint of 1024 quadrupeds, 256 waves,
+// one / two / four per block: 2859 / 2968 / 3062 us; forward 1126 / 1187 /
+// 1150; tangents of 1000 trees, 360 waves, 183 / 187 / 199; no difference from
+// 1000 waves up).
 template <typename S, bool C>
 int single_wpb(const Tiling& tl, int nwaves, size_t& lds) {
-  int w = tl.waves_per_block;
+  int w = tl.chosen ? tl.waves_per_block : 1;
   if (w != 1 && w != 2 && w != 4) w = 1;
   const size_t per = C ? 0 : (size_t)XB * kWave * sizeof(S);
   while (w > 1 && (per * w > lds_limit() || nwaves % w != 0)) w /= 2;
@@ -1599,11 +1651,11 @@ hipError_t launch_backward_planar(const BwdArgs<S>& a, const Tiling& tl, hipStre
   return hipGetLastError();
 }
 
-template <typename S, typename R, bool F, int E, bool C, bool PARAMS>
+template <typename S, typename R, bool F, int E, bool C, bool PARAMS, bool FRAME = false>
 hipError_t launch_backward_one(const BwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
   size_t lds = 0;
-  const int w = single_wpb<R, C>(tl, a.P.nwaves, lds);
-  hipLaunchKernelGGL((k_backward<S, R, F, E, C, PARAMS>), dim3(a.P.nwaves / w), dim3(kWave * w), lds, st, a);
+  const int w = single_wpb<R, C && !FRAME>(tl, a.P.nwaves, lds);
+  hipLaunchKernelGGL((k_backward<S, R, F, E, C, PARAMS, FRAME>), dim3(a.P.nwaves / w), dim3(kWave * w), lds, st, a);
   return hipGetLastError();
 }
 
@@ -1613,6 +1665,9 @@ hipError_t launch_backward_p(const BwdArgs<S>& a, const Tiling& tl, hipStream_t 
   // (K == 0) and the FP32 reverse stay with the general kernels
   if constexpr (C && E == kFrIdentity && !PARAMS && sizeof(R) == sizeof(double)) {
     if (a.K != 0) return launch_backward_planar(a, tl, st);
+    return launch_backward_one<S, R, F, E, C, PARAMS>(a, tl, st);
+  } else if constexpr (!PARAMS && sizeof(R) == sizeof(double)) {
+    if (a.K != 0) return launch_backward_one<S, R, F, E, C, PARAMS, true>(a, tl, st);
     return launch_backward_one<S, R, F, E, C, PARAMS>(a, tl, st);
   } else if (a.K == 1 && tl.pipelined) {
     const size_t per = pipe_lds_per_pair<S, R, F, E, C>();

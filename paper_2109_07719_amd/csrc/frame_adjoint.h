@@ -1,0 +1,568 @@
+// The FP64 adjoint of trees, free roots, prismatic and ball joints and joint
+// limits, in the base frame, by the adjoint of the inverse dynamics: with w =
+// M^-1 (dt qd1_bar) (two sweeps with the step's articulated factors),
+//   tau_bar = w,  (q_bar, qd_bar) -= d/d(q, qd) <w, ID(q, qd, qdd)> at fixed qdd
+// (the derivative of M qdd + C(q, qd) = tau).  Sec. 3, Eq. adj_back; Sec. 4.1,
+// Eq. adj_r.  Included by abadj_device.h after the general backward kernels.
+//
+// What bounds these kernels is the instructions a wavefront issues over the
+// levels of a tree, where one lane in six works.  So every spatial quantity is
+// taken about one origin in one frame (a fixed base's; a free root's own,
+// where its motion subspace is the identity): the level loops then add and
+// transform nothing, poses and velocities come from ancestor-doubling rounds
+// (log2 of the depth) instead of levels, and what the reverse needs beyond
+// the two sweeps is one sum over each subtree.  Adjoints of 8192 trees x 50
+// steps 2.83 -> 1.60 ms, of 1024 quadrupeds x 200 steps in segments of 10
+// (replay included) 4.74 -> 2.86 ms.
+//
+// A ball joint's three axes turn with its link; its subspace is every
+// rotation about the joint's origin o, S = [1; [o]x], and its block form is
+// taken about o, where S = [1; 0] (aba_lane.h, "ball joint").
+#pragma once
+
+#include "planar_adjoint.h"
+
+namespace aba {
+
+namespace {
+
+constexpr int kJumps = 6;  // doubling rounds for up to 64 levels
+
+// The link's constants stay in the handle's type S (FP32 ones widen exactly
+// where they are used, at a third of the registers' cost).
+template <typename S>
+struct FrameLane {
+  int lane, par, dep, cf, cc, maxd;
+  int base;         // the lane of the system's free root, -1 without one
+  int anc[kJumps];  // the lane 1, 2, 4, ... levels up, -1 past the root
+  bool act, one, root, ball, prism;
+  LinkC<S> L;
+  V3<S> g;
+};
+
+template <typename S, int FR>
+__device__ __forceinline__ FrameLane<S> frame_lane(const Packed<S>& P, const Lane& l, int maxd) {
+  FrameLane<S> p;
+  p.L = load_linkc<S, FR>(P, l);
+  p.lane = l.lane;
+  p.par = l.active() ? l.par : -1;
+  p.dep = l.active() ? l.depth : -1;
+  p.cf = l.cfirst;
+  p.cc = l.active() ? l.ccount : 0;
+  p.maxd = maxd;
+  p.act = l.active();
+  p.one = l.onedof() && l.active();
+  p.root = l.jtype == 1;
+  p.ball = FR == kFrBall && l.ball();
+  p.prism = p.L.prism;
+  p.g = gravity(P);
+  int a = p.par;
+#pragma unroll
+  for (int r = 0; r < kJumps; ++r) {
+    p.anc[r] = a;
+    const int up = __shfl(a, a < 0 ? 0 : a);
+    a = a < 0 ? -1 : up;
+  }
+  p.base = p.root ? p.lane : -1;
+#pragma unroll
+  for (int r = 0; r < kJumps; ++r) {
+    const int b = __shfl(p.base, p.anc[r] < 0 ? 0 : p.anc[r]);
+    if (p.anc[r] >= 0 && p.base < 0) p.base = b;
+  }
+  return p;
+}
+
+// v summed over the link and its ancestors, by doubling rounds through the
+// exchange records (a round: one write and one read of every lane).
+template <typename S>
+__device__ __forceinline__ V6<double> path_sum(const FrameLane<S>& p, V6<double> v, double* xb) {
+#pragma unroll
+  for (int r = 0; r < kJumps; ++r) {
+    if (1 << r > p.maxd) break;
+    put6(xb, 0, p.lane, v);
+    wave_sync();
+    if (p.anc[r] >= 0) v = get6(xb, 0, p.anc[r]) + v;
+    wave_sync();
+  }
+  return v;
+}
+
+// A step's quantities that its reverse reads.  A free root keeps its 6 x 6
+// factor M = L^T D L in S, U, Di, Ap, F (root_pack), which it does not use.
+struct FrameStep {
+  V6<double> S, U, V, Ap, F;
+  double Di;
+  V3<double> mc;
+  Sy3<double> I;
+  double q, qd;          // 1-dof joint
+  V6<double> abase;      // free root: acceleration; ball: [acceleration, o]
+  // ball joint
+  M3<double> R, B;       // pose; the articulated inertia's coupling block about o
+  Sy3<double> Ai;        // inverse of its angular block
+};
+
+struct RootF {
+  double L[15], iv[6];
+};
+__device__ __forceinline__ void root_pack(FrameStep& o, const RootF& f) {
+  const double* L = f.L;
+  o.S = v6<double>(v3<double>(L[0], L[1], L[2]), v3<double>(L[3], L[4], L[5]));
+  o.U = v6<double>(v3<double>(L[6], L[7], L[8]), v3<double>(L[9], L[10], L[11]));
+  o.Di = L[12];
+  o.Ap = v6<double>(v3<double>(L[13], L[14], f.iv[0]), v3<double>(f.iv[1], f.iv[2], f.iv[3]));
+  o.F = v6<double>(v3<double>(f.iv[4], f.iv[5], 0.0), zero3<double>());
+}
+__device__ __forceinline__ RootF root_unpack(const FrameStep& o) {
+  return {{o.S.a.x, o.S.a.y, o.S.a.z, o.S.l.x, o.S.l.y, o.S.l.z, o.U.a.x, o.U.a.y, o.U.a.z, o.U.l.x, o.U.l.y,
+           o.U.l.z, o.Di, o.Ap.a.x, o.Ap.a.y},
+          {o.Ap.a.z, o.Ap.l.x, o.Ap.l.y, o.Ap.l.z, o.F.a.x, o.F.a.y}};
+}
+__device__ __forceinline__ RootF root_factor(const SySp<double>& IA) {
+  double M[36];
+  sysp_dense(IA, M);
+  RootF f;
+#pragma unroll
+  for (int k = 5; k >= 0; --k) {
+    f.iv[k] = fast_rcp(M[7 * k]);
+#pragma unroll
+    for (int i = 0; i < k; ++i) {
+      const double c = M[6 * k + i] * f.iv[k];
+      f.L[k * (k - 1) / 2 + i] = c;
+#pragma unroll
+      for (int j = 0; j <= i; ++j) M[6 * i + j] = fma(-c, M[6 * k + j], M[6 * i + j]);
+    }
+  }
+  return f;
+}
+__device__ __forceinline__ V6<double> root_solve(const RootF& f, const V6<double>& b) {
+  double r[6] = {b.a.x, b.a.y, b.a.z, b.l.x, b.l.y, b.l.z};
+#pragma unroll
+  for (int e = 5; e >= 0; --e)
+#pragma unroll
+    for (int i = 0; i < e; ++i) r[i] = fma(-f.L[e * (e - 1) / 2 + i], r[e], r[i]);
+#pragma unroll
+  for (int e = 0; e < 6; ++e) {
+    double v = r[e] * f.iv[e];
+#pragma unroll
+    for (int i = 0; i < e; ++i) v = fma(-f.L[e * (e - 1) / 2 + i], r[i], v);
+    r[e] = v;
+  }
+  return v6<double>(v3<double>(r[0], r[1], r[2]), v3<double>(r[3], r[4], r[5]));
+}
+
+// a symmetric spatial inertia, and a force, moved from the base's origin to o
+__device__ __forceinline__ SySp<double> about(const SySp<double>& M, const V3<double>& o) {
+  // X = [1 0; [o]x 1] maps motions about o to the base's: M' = X^T M X
+  M3<double> E;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) E.m[k] = k % 4 == 0 ? 1.0 : 0.0;
+  return congruence_XT(E, -o, M);
+}
+__device__ __forceinline__ V3<double> moment_at(const V6<double>& f, const V3<double>& o) { return f.a - cross(o, f.l); }
+// [n about o; f] about the base's origin
+__device__ __forceinline__ V6<double> from_point(const V3<double>& n, const V3<double>& f, const V3<double>& o) {
+  return v6<double>(n + cross(o, f), f);
+}
+
+template <bool FREE, bool BALL, typename S>
+__device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, const State<double, FREE>& st,
+                                                     const V3<double>& ctl, double* xb) {
+  FrameStep o;
+  const V3<double> z3 = zero3<double>();
+  o.q = st.q[0];
+  o.qd = st.qd[0];
+  o.abase = zero6<double>();
+  // ---- poses by doubling rounds
+  M3<double> R;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) R.m[k] = k % 4 == 0 ? 1.0 : 0.0;
+  V3<double> org = z3;
+  const V3<double> grav = widen<double>(p.g);
+  V3<double> gb = grav;
+  const M3<double> ETt = widen<double>(transpose(p.L.ET));
+  const double m = double(p.L.m);
+  if (p.one) {
+    org = widen<double>(p.L.rT);
+    R = ETt;
+    if (p.prism) {
+      org = axpy(org, o.q, col(ETt, 2));
+    } else {
+      double sn, cs;
+      sincos(o.q, &sn, &cs);
+      // E_T^T times the rotation by q about z
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        R.m[3 * i] = cs * ETt.m[3 * i] + sn * ETt.m[3 * i + 1];
+        R.m[3 * i + 1] = cs * ETt.m[3 * i + 1] - sn * ETt.m[3 * i];
+      }
+    }
+  }
+  if constexpr (BALL) {
+    if (p.ball) {
+      org = widen<double>(p.L.rT);
+      const Q4<double> q = st_ball_quat(st);
+      M3<double> Q;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const V3<double> c = quat_rotate(q, v3<double>(double(j == 0), double(j == 1), double(j == 2)));
+        Q.m[j] = c.x;
+        Q.m[3 + j] = c.y;
+        Q.m[6 + j] = c.z;
+      }
+      R = mul(ETt, Q);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kJumps; ++r) {
+    if (1 << r > p.maxd) break;
+    const double t[12] = {R.m[0], R.m[1], R.m[2], R.m[3], R.m[4], R.m[5], R.m[6], R.m[7], R.m[8], org.x, org.y, org.z};
+    put_rec(xb, p.lane, 0, t);
+    wave_sync();
+    if (p.anc[r] >= 0) {
+      double u[12];
+      get_rec(xb, p.anc[r], 0, u);
+      M3<double> Rp;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) Rp.m[k] = u[k];
+      org = v3<double>(u[9], u[10], u[11]) + mul(Rp, org);
+      R = mul(Rp, R);
+    }
+    wave_sync();
+  }
+  // ---- velocities and bias accelerations (a free root's in the frame that
+  // moves with its linear velocity, an exact shift)
+  const V3<double> ax = col(R, 2);
+  o.S = zero6<double>();
+  V6<double> vJ = zero6<double>();
+  if (p.one) {
+    o.S = p.prism ? v6<double>(z3, ax) : v6<double>(ax, cross(org, ax));
+    vJ = o.qd * o.S;
+  }
+  if constexpr (BALL) {
+    if (p.ball) {
+      const V3<double> w = mul(R, st_ball_w(st));
+      vJ = v6<double>(w, cross(org, w));
+    }
+  }
+  if constexpr (FREE) {
+    if (p.root) vJ = v6<double>(st_vel6(st).a, z3);
+  }
+  o.V = path_sum(p, vJ, xb);
+  if constexpr (FREE) {
+    // gravity in the root's frame, for its whole system
+    const V3<double> gr = quat_rotate_T(st_quat(st), grav);
+    const int from = p.base < 0 ? 0 : p.base;
+    const V3<double> t = v3<double>(__shfl(gr.x, from), __shfl(gr.y, from), __shfl(gr.z, from));
+    if (p.base >= 0) gb = t;
+  }
+  const V6<double> cb = p.root ? zero6<double>() : crm(o.V, vJ);
+  const V6<double> A0 = path_sum(p, cb, xb) - v6<double>(z3, gb);
+  // ---- inertia about the base's origin, bias force
+  const V3<double> Rmc = mul(R, widen<double>(p.L.mc));
+  o.mc = axpy(Rmc, m, org);
+  {
+    // I + [terms of the shift by org]: (2 org.Rmc + m org^2) 1 - sym(org, Rmc) ...
+    const Sy3<double> J = cong(R, widen<double>(p.L.Ib));
+    const double d = dot(org, Rmc) + dot(org, o.mc);
+    o.I = sy3<double>(J.xx + d - (org.x * Rmc.x + o.mc.x * org.x), J.yy + d - (org.y * Rmc.y + o.mc.y * org.y),
+                      J.zz + d - (org.z * Rmc.z + o.mc.z * org.z), J.xy - (org.x * Rmc.y + o.mc.x * org.y),
+                      J.xz - (org.x * Rmc.z + o.mc.x * org.z), J.yz - (org.y * Rmc.z + o.mc.y * org.z));
+  }
+  LinkC<double> body;  // inertia_mul's view of it
+  body.m = m;
+  body.mc = o.mc;
+  body.Ib = o.I;
+  V6<double> F = inertia_mul(body, A0) + crf(o.V, inertia_mul(body, o.V));
+  SySp<double> IA = inertia_sysp(body);
+  // ---- articulated inertias and bias forces, leaves to root
+  double u = 0;
+  V3<double> ub = z3, yb = z3;
+  o.U = zero6<double>();
+  o.Di = 0;
+  V3<double> tb = z3;
+  if constexpr (BALL) {
+    if (p.ball) tb = mul(R, ctl);
+  }
+  for (int d = p.maxd; d >= 0; --d) {
+    if (p.dep == d) {
+      for (int c = 0; c < p.cc; ++c) {
+        SySp<double> Ic;
+        V6<double> Fc;
+        get27(xb, p.cf + c, Ic, Fc);
+        IA = IA + Ic;
+        F = F + Fc;
+      }
+      if (p.one) {
+        o.U = mul(IA, o.S);
+        o.Di = fast_rcp(dot(o.S, o.U));
+        u = ctl.x - dot(o.S, F);
+        if (p.par >= 0) {
+          put27(xb, p.lane, rank1_down(IA, o.U, o.Di), F + (u * o.Di) * o.U);
+        }
+      }
+      if constexpr (BALL) {
+        if (p.ball) {
+          const SySp<double> Io = about(IA, org);
+          o.Ai = sy3_inv(Io.A);
+          o.B = Io.B;
+          ub = tb - moment_at(F, org);
+          yb = mul(o.Ai, ub);
+          if (p.par >= 0) {
+            const M3<double> W = mul(sy_to_m3(o.Ai), o.B);
+            const M3<double> BW = mul(transpose(o.B), W);
+            SySp<double> Ia = zero_sysp<double>();
+            Ia.C = Io.C - sy3<double>(BW.m[0], BW.m[4], BW.m[8], BW.m[1], BW.m[2], BW.m[5]);
+            put27(xb, p.lane, about(Ia, -org), from_point(tb, F.l + mulT(o.B, yb), org));
+          }
+        }
+      }
+    }
+    wave_sync();
+  }
+  // ---- accelerations, root to leaves
+  RootF f;
+  V6<double> a = zero6<double>(), ap = zero6<double>();
+  double qdd = 0;
+  if constexpr (FREE) {
+    if (p.root) {
+      f = root_factor(IA);
+      a = root_solve(f, v6<double>(-F.a, -F.l));
+      const V6<double> v = st_vel6(st);
+      o.abase = v6<double>(a.a, a.l - cross(v.a, v.l));
+    }
+  }
+  for (int d = 0; d <= p.maxd; ++d) {
+    if (p.dep == d) {
+      if (p.par >= 0) ap = get6(xb, 0, p.par);
+      if (p.one) {
+        qdd = (u - dot(o.U, ap)) * o.Di;
+        a = ap + qdd * o.S;
+      }
+      if constexpr (BALL) {
+        if (p.ball) {
+          const V3<double> lo = ap.l + cross(ap.a, org);
+          const V3<double> Wl = mul(o.Ai, mul(o.B, lo)), al = yb - Wl;
+          const V3<double> acc = mulT(R, al - ap.a);  // in link coordinates, as the rate
+          a = v6<double>(al, lo - cross(al, org));
+          o.abase = v6<double>(acc, org);
+        }
+      }
+      if (p.cc) put6(xb, 0, p.lane, a);
+    }
+    wave_sync();
+  }
+  o.F = mul(IA, a) + F;
+  o.Ap = ap + A0 - cb;
+  if constexpr (FREE) {
+    if (p.root) root_pack(o, f);
+  }
+  if constexpr (BALL) o.R = R;
+  return o;
+}
+
+// w = M^-1 r with the step's factors (r, r3, r6: the right-hand side of a
+// 1-dof, ball and root lane, replaced by the solution); B: the spatial
+// accelerations of the response, Bp the parent's.
+template <bool FREE, bool BALL, typename S>
+__device__ __forceinline__ void frame_solve(const FrameLane<S>& p, const FrameStep& o, double& r, V3<double>& r3,
+                                            V6<double>& r6, V6<double>& B, V6<double>& Bp, double* xb) {
+  const V3<double> org = o.abase.l;  // ball lanes
+  V3<double> y3 = zero3<double>();
+  for (int d = p.maxd; d >= 0; --d) {
+    if (p.dep == d) {
+      V6<double> s = zero6<double>();
+      for (int c = 0; c < p.cc; ++c) s = s + get6(xb, 0, p.cf + c);
+      if (p.one) {
+        r = r - dot(o.S, s);
+        if (p.par >= 0) put6(xb, 0, p.lane, s + (r * o.Di) * o.U);
+      }
+      if constexpr (BALL) {
+        if (p.ball) {
+          const V3<double> r0 = r3;
+          y3 = mul(o.Ai, r0 - moment_at(s, org));
+          if (p.par >= 0) put6(xb, 0, p.lane, from_point(r0, s.l + mulT(o.B, y3), org));
+        }
+      }
+      if constexpr (FREE) {
+        if (p.root) r6 = r6 - s;
+      }
+    }
+    wave_sync();
+  }
+  B = Bp = zero6<double>();
+  if constexpr (FREE) {
+    if (p.root) {
+      r6 = root_solve(root_unpack(o), r6);
+      B = r6;
+    }
+  }
+  for (int d = 0; d <= p.maxd; ++d) {
+    if (p.dep == d) {
+      if (p.par >= 0) Bp = get6(xb, 0, p.par);
+      if (p.one) {
+        r = (r - dot(o.U, Bp)) * o.Di;
+        B = Bp + r * o.S;
+      }
+      if constexpr (BALL) {
+        if (p.ball) {
+          const V3<double> lo = Bp.l + cross(Bp.a, org);
+          const V3<double> al = y3 - mul(o.Ai, mul(o.B, lo));
+          r3 = al - Bp.a;
+          B = v6<double>(al, lo - cross(al, org));
+        }
+      }
+      if (p.cc) put6(xb, 0, p.lane, B);
+    }
+    wave_sync();
+  }
+}
+
+// The adjoint of the step from st: x1 in, the adjoint of (q1, qd1), and out,
+// that of (q, qd); returns the lane's tau_bar.  lq, lqd: the joint-limit
+// torque's slopes.
+template <bool FREE, bool BALL, typename S>
+__device__ __forceinline__ V3<double> frame_reverse(const FrameLane<S>& p, const FrameStep& o,
+                                                    const State<double, FREE>& st, double dt, double lq, double lqd,
+                                                    State<double, FREE>& x1, double* xb) {
+  // ---- integrator
+  const double tot = x1.qd[0] + dt * x1.q[0];
+  double r = dt * tot;
+  V6<double> g6 = zero6<double>(), r6 = zero6<double>();
+  V3<double> pb = zero3<double>(), r3 = zero3<double>(), wb = zero3<double>();
+  Q4<double> qb = {0, 0, 0, 0};
+  if constexpr (FREE) {
+    if (p.root) {
+      pb = v3<double>(x1.q[0], x1.q[1], x1.q[2]);
+      qb = {x1.q[3], x1.q[4], x1.q[5], x1.q[6]};
+      g6 = st_vel6(x1);
+      r6 = integrate_root_adj(st_quat(st), st_vel6(st), o.abase, dt, pb, qb, g6);
+    }
+  }
+  if constexpr (BALL) {
+    if (p.ball) {
+      wb = st_ball_w(x1);
+      qb = quat_step_adj(st_ball_quat(st), st_ball_w(st) + dt * o.abase.a, dt, st_ball_quat(x1), wb);
+      r3 = dt * mul(o.R, wb);
+    }
+  }
+  // ---- w = M^-1 (dt qd1_bar)
+  V6<double> B, Bp;
+  frame_solve<FREE, BALL>(p, o, r, r3, r6, B, Bp, xb);
+  // ---- <w, ID> = sum_i B_i . (I A + V x* I V): per link its share of A's
+  // adjoint, I B, and of V's (the bias accelerations V_l x S_l qd_l from the
+  // root to link i sum to V_i in the second), summed over subtrees
+  LinkC<double> body;
+  body.m = double(p.L.m);
+  body.mc = o.mc;
+  body.Ib = o.I;
+  V6<double> G = inertia_mul(body, B);
+  V6<double> e = crmT(B, inertia_mul(body, o.V)) - inertia_mul(body, crm(o.V, B)) - crmT(o.V, G);
+  for (int d = p.maxd; d >= 0; --d) {
+    if (p.dep == d) {
+      for (int c = 0; c < p.cc; ++c) {
+        G = G + get6(xb, 0, p.cf + c);
+        e = e + get6(xb, 6, p.cf + c);
+      }
+      if (p.par >= 0) {
+        put6(xb, 0, p.lane, G);
+        put6(xb, 6, p.lane, e);
+      }
+    }
+    wave_sync();
+  }
+  // ---- the subtree turns with q: what enters it from the parent turns back
+  V3<double> taub = zero3<double>();
+  if (p.one) {
+    const V6<double> Vp = o.V - o.qd * o.S;
+    const V6<double> vb = e + crmT(Vp, G);
+    const double qE = dot(o.S, crf(Bp, o.F) + crf(o.Ap, G) + crf(Vp, vb));
+    const double qdE = dot(o.S, crmT(o.V, G) + vb);
+    x1.q[0] = x1.q[0] + qE + lq * r;
+    x1.qd[0] = tot - qdE + lqd * r;
+    taub.x = r;
+  }
+  if constexpr (BALL) {
+    if (p.ball) {
+      const V3<double> org = o.abase.l, w = mul(o.R, st_ball_w(st));
+      const V6<double> Vp = o.V - v6<double>(w, cross(org, w));
+      const V6<double> vb = e + crmT(Vp, G);
+      const V3<double> turn = mulT(o.R, moment_at(crf(Bp, o.F) + crf(o.Ap, G) + crf(Vp, vb), org));
+      const V3<double> rate = mulT(o.R, moment_at(crmT(o.V, G) + vb, org));
+      const Q4<double> t = ball_quat_bar(st_ball_quat(st), turn);
+      x1.q[0] = qb.x + t.x;
+      x1.q[1] = qb.y + t.y;
+      x1.q[2] = qb.z + t.z;
+      x1.q[3] = qb.w + t.w;
+      x1.qd[0] = wb.x - rate.x;
+      x1.qd[1] = wb.y - rate.y;
+      x1.qd[2] = wb.z - rate.z;
+      taub = mulT(o.R, r3);
+    }
+  }
+  if constexpr (FREE) {
+    if (p.root) {
+      // the root's velocity entered as [w; 0], its acceleration as qdd +
+      // [0; w x v] - [0; R^T g]
+      const V6<double> v = st_vel6(st);
+      const Q4<double> t = quat_rot_grad(st_quat(st), widen<double>(p.g), G.l);
+      const V3<double> wv = g6.a - (e.a + crmT(o.V, G).a) - cross(v.l, G.l);
+      const V3<double> lv = g6.l - cross(G.l, v.a);
+      x1.q[0] = pb.x;
+      x1.q[1] = pb.y;
+      x1.q[2] = pb.z;
+      x1.q[3] = qb.x + t.x;
+      x1.q[4] = qb.y + t.y;
+      x1.q[5] = qb.z + t.z;
+      x1.q[6] = qb.w + t.w;
+      x1.qd[0] = wv.x;
+      x1.qd[1] = wv.y;
+      x1.qd[2] = wv.z;
+      x1.qd[3] = lv.x;
+      x1.qd[4] = lv.y;
+      x1.qd[5] = lv.z;
+    }
+  }
+  return taub;
+}
+
+// A step's reverse in the backward rollout: recompute and reverse from the
+// stored state and control, then tau_bar out and the trajectory's seed of x^t
+// in.
+template <typename S, bool FREE>
+__device__ __forceinline__ void frame_outputs(const BwdArgs<S>& A, const Lane& l, int t, const V3<double>& taub,
+                                              State<double, FREE>& x1, int& nonfin) {
+  if (!l.active()) return;
+  const S tb[3] = {S(taub.x), S(taub.y), S(taub.z)};
+  const int n = l.onedof() ? 1 : l.ball() ? 3 : 0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    if (k < n) {
+      A.gtau[(size_t)t * A.P.nu + l.uidx + k] = tb[k];
+      nonfin += nonfinite(tb[k]);
+    }
+  if (A.gtraj != nullptr && t >= 1) {
+    State<S, FREE> gt = {};
+    const S* row = A.gtraj + (size_t)(t - 1) * (A.P.nq + A.P.nv);
+    load_state(gt, l, row, row + A.P.nq);
+#pragma unroll
+    for (int k = 0; k < (FREE ? 7 : 1); ++k) x1.q[k] += double(gt.q[k]);
+#pragma unroll
+    for (int k = 0; k < (FREE ? 6 : 1); ++k) x1.qd[k] += double(gt.qd[k]);
+  }
+}
+template <typename S, bool FREE, int FR>
+__device__ __forceinline__ void frame_step(const BwdArgs<S>& A, const Lane& l, const FrameLane<S>& p, double* xb,
+                                           const State<S, FREE>& st, const V3<S>& tau, int t, State<double, FREE>& x1,
+                                           int& nonfin) {
+  constexpr bool BALL = FREE && FR == kFrBall;
+  const State<double, FREE> sr = cvt_state<double>(st);
+  const FrameStep o = frame_recompute<FREE, BALL>(p, sr, limit_tau<FR>(A.P, l, sr, cvt3<double>(tau)), xb);
+  double lq, lqd;
+  limit_slopes<FR>(A.P, l, sr, lq, lqd);
+  const V3<double> taub = frame_reverse<FREE, BALL>(p, o, sr, double(A.dt), lq, lqd, x1, xb);
+  frame_outputs<S, FREE>(A, l, t, taub, x1, nonfin);
+}
+
+}  // namespace
+
+}  // namespace aba
