@@ -1659,6 +1659,36 @@ hipError_t launch_backward_one(const BwdArgs<S>& a, const Tiling& tl, hipStream_
   return hipGetLastError();
 }
 
+// The pipelined base-frame adjoint, if its LDS fits and the batches take at
+// most `rounds` rounds of resident workgroups (0: any number).
+template <typename S, bool F, int E, int NP, int NR>
+bool launch_frame_pipe(const BwdArgs<S>& a, size_t rounds, hipStream_t st) {
+  const size_t lds = FramePipe<S, F, E, NP, NR>::lds(a.K, a.P.mfree), limit = lds_limit();
+  if (lds > limit) return false;
+  if (rounds > 0 && (size_t)a.P.nwaves > rounds * (simd_count() / 4) * (limit / lds)) return false;
+  hipLaunchKernelGGL((k_backward_frame_pipe<S, F, E, NP, NR>), dim3(a.P.nwaves), dim3((NP + NR + 1) * kWave), lds, st, a);
+  return true;
+}
+template <typename S, bool F, int E, bool C>
+hipError_t launch_backward_frame(const BwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
+  // A pipelined batch takes a third to a half of one wavefront's time, but a
+  // CU's LDS holds one or two, where its SIMDs hold four single waves: K == 1
+  // is pipelined while every batch is resident at once (or as chosen), with
+  // two recomputing wavefronts if those fit too; K > 1 up to two rounds
+  // (40 steps, us, one wave / NP = 1 / NP = 2; K = 1: quadrupeds, 256 batches
+  // 365 / 235 / 186, 512 381 / 258 / 368, 768 409 / 507 / 551; trees, 384 575
+  // / 355 / 409, 744 616 / 691 / 637; ball quadrupeds, 256 494 / 289, 512 514 /
+  // 575.  K = 10: quadrupeds, 256 576 / 296, 512 600 / 583, 768 621 / 873; ball
+  // quadrupeds, 512 730 / 665, 768 763 / 1002; trees, 384 844 / 688, 744 885 /
+  // 1089).  One step has nothing to overlap.
+  if (a.K == 1 && a.T > 1 && (!tl.chosen || tl.pipelined)) {
+    if (launch_frame_pipe<S, F, E, 2, 0>(a, 1, st) || launch_frame_pipe<S, F, E, 1, 0>(a, tl.chosen ? 0 : 1, st))
+      return hipGetLastError();
+  }
+  if (a.K > 1 && a.T > 1 && launch_frame_pipe<S, F, E, 1, 1>(a, 2, st)) return hipGetLastError();
+  return launch_backward_one<S, double, F, E, C, false, true>(a, tl, st);
+}
+
 template <typename S, typename R, bool F, int E, bool C, bool PARAMS>
 hipError_t launch_backward_p(const BwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
   // planar chains; the model-parameter gradients, the stored intermediates
@@ -1667,7 +1697,7 @@ hipError_t launch_backward_p(const BwdArgs<S>& a, const Tiling& tl, hipStream_t 
     if (a.K != 0) return launch_backward_planar(a, tl, st);
     return launch_backward_one<S, R, F, E, C, PARAMS>(a, tl, st);
   } else if constexpr (!PARAMS && sizeof(R) == sizeof(double)) {
-    if (a.K != 0) return launch_backward_one<S, R, F, E, C, PARAMS, true>(a, tl, st);
+    if (a.K != 0) return launch_backward_frame<S, F, E, C>(a, tl, st);
     return launch_backward_one<S, R, F, E, C, PARAMS>(a, tl, st);
   } else if (a.K == 1 && tl.pipelined) {
     const size_t per = pipe_lds_per_pair<S, R, F, E, C>();

@@ -36,7 +36,8 @@ struct Packed {
   const int32_t* wmaxd;  // [nwaves] deepest level present in each wave
   int nslots;
   int nwaves;
-  int nfree;             // number of free-floating roots in the batch
+  int nfree;             // number of free-floating roots and ball joints in the batch
+  int mfree;             // the most of them in one wave
   S g[3];                // gravity
   int nq, nv, nu;        // totals over the batch
   unsigned long long* status;  // device counter of non-finite numbers written to outputs

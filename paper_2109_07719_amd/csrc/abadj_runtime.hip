@@ -46,7 +46,7 @@ constexpr int kMaxSnapshots = 4096;
 struct sim_handle {
   int dtype = SIM_F32;
   int n_sys = 0, n_links = 0, nq = 0, nv = 0, nu = 0;
-  int nwaves = 0, nslots = 0, max_depth = 0, nfree = 0;
+  int nwaves = 0, nslots = 0, max_depth = 0, nfree = 0, mfree = 0;
   bool has_free = false;
   bool eti = false;  // every joint frame is the identity after canonicalisation
   bool chain = false;  // every system is a fixed-base serial chain of revolute joints
@@ -118,6 +118,7 @@ aba::Packed<S> packed(const sim_handle* h) {
   P.nslots = h->nslots;
   P.nwaves = h->nwaves;
   P.nfree = h->nfree;
+  P.mfree = h->mfree;
   for (int k = 0; k < 3; ++k) P.g[k] = static_cast<S>(h->g[k]);
   P.nq = h->nq;
   P.nv = h->nv;
@@ -571,6 +572,11 @@ int sim_create(const sim_topology* topo, const sim_params* prm, int dtype, sim_t
   }
   h->chain = chain;
   h->tiling = default_tiling(h->nwaves);
+  for (int w = 0; w < h->nwaves; ++w) {
+    int m = 0;
+    for (int lane = 0; lane < aba::kWave; ++lane) m += ci[(size_t)aba::CI_FIDX * NS + w * aba::kWave + lane] >= 0;
+    h->mfree = std::max(h->mfree, m);
+  }
   std::vector<int32_t> wmaxd(wave_depth.begin(), wave_depth.end());
   {
     // FNV-1a over the structure: every packed integer field except the

@@ -563,6 +563,180 @@ __device__ __forceinline__ void frame_step(const BwdArgs<S>& A, const Lane& l, c
   frame_outputs<S, FREE>(A, l, t, taub, x1, nonfin);
 }
 
+// A step's record in LDS, [field][lane]: what the reverse reads of a recompute.
+template <bool FREE, bool BALL>
+constexpr int kFrameTape = 42 + (FREE ? 6 : 0) + (BALL ? 24 : 0);
+template <bool FREE, bool BALL, typename F>
+__device__ __forceinline__ void frame_fields(FrameStep& o, F&& f) {
+  int k = 0;
+  auto w = [&](double& x) { f(k++, x); };
+  auto w3 = [&](V3<double>& v) { w(v.x); w(v.y); w(v.z); };
+  auto w6 = [&](V6<double>& v) { w3(v.a); w3(v.l); };
+  auto ws = [&](Sy3<double>& m) { w(m.xx); w(m.yy); w(m.zz); w(m.xy); w(m.xz); w(m.yz); };
+  w6(o.S); w6(o.U); w6(o.V); w6(o.Ap); w6(o.F);
+  w(o.Di);
+  w3(o.mc);
+  ws(o.I);
+  w(o.q);
+  w(o.qd);
+  if constexpr (FREE) w6(o.abase);
+  if constexpr (BALL) {
+#pragma unroll
+    for (int j = 0; j < 9; ++j) w(o.R.m[j]);
+#pragma unroll
+    for (int j = 0; j < 9; ++j) w(o.B.m[j]);
+    ws(o.Ai);
+  }
+}
+
+// The wavefronts of the pipelined backward on one batch, and its LDS: NR
+// replaying (K > 1), NP recomputing, one reversing.
+template <typename S, bool FREE, int FR, int NP, int NR>
+struct FramePipe {
+  static constexpr bool BALL = FREE && FR == kFrBall;
+  static constexpr int waves = NR + NP + 1;
+  static constexpr int TW = kFrameTape<FREE, BALL> * kWave;
+  static constexpr size_t rec = XB * kWave;  // one exchange buffer
+  // numbers of a replayed state in the ring (slots, then mfree extended ones)
+  static __host__ __device__ int state(int mfree) { return 2 * kWave + 11 * mfree; }
+  static __host__ __device__ size_t lds(int K, int mfree) {
+    return (size_t)(2 * NP * TW + (NP + 1) * rec) * sizeof(double) +
+           NR * ((size_t)3 * K * state(mfree) + rec) * sizeof(S);
+  }
+};
+
+// Pipelined backward rollout, K >= 1, in phases of NP steps ended by a
+// workgroup barrier.  The recomputes do not depend on one another: in phase k
+// producer j recomputes the phase's step j into buffer k % 2 while the consumer
+// reverses the steps of phase k - 1.  K > 1 (NR = 1): one more wavefront
+// replays the segment before, a share of its steps each phase, into a ring of
+// three segments of states in LDS (one replayed, one recomputed, the last
+// steps of one still to be reversed), so that a segment costs its slowest
+// part and not replay, recompute and reverse in turn.  The reversing wavefront
+// bounds K == 1 with two recomputing ones (4.6 us a step of a quadruped), the
+// recomputing one K > 1 (6 us).  Adjoints of 1024 quadrupeds x 200 steps in
+// segments of 10, 2.86 -> 1.24 ms; of 1024 ball-jointed ones x 100 steps, K =
+// 1, 1.22 -> 0.70 ms.
+template <typename S, bool FREE, int FR, int NP, int NR>
+__global__ __launch_bounds__((NP + NR + 1) * kWave)
+__attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(BwdArgs<S> A) {
+  using P = FramePipe<S, FREE, FR, NP, NR>;
+  constexpr bool BALL = P::BALL;
+  const int wid = threadIdx.x / kWave;
+  double* const tape = lds<double>();
+  double* const xbs = tape + 2 * NP * P::TW;
+  S* const xreplay = reinterpret_cast<S*>(xbs + (NP + 1) * P::rec);
+  S* const ring = xreplay + P::rec;
+  const int wb = blockIdx.x;
+  const Lane l = load_lane(A.P, wb);
+  const int maxd = wave_maxd(A.P, wb);
+  const int ns = A.P.nslots, nu = A.P.nu, nf = A.P.nfree, mf = A.P.mfree, T = A.T;
+  const size_t RW = state_record(ns, nf);
+  const bool act = l.active();
+  // K > 1: segments last to first, each ppseg phases; replay runs ppseg
+  // phases ahead.  K == 1: one segment of T steps
+  const int seg = NR ? A.K : T, nseg = (T + seg - 1) / seg;
+  const int ppseg = (seg + NP - 1) / NP, ahead = NR ? ppseg : 0, phases = ahead + nseg * ppseg;
+  const unsigned long long extended = __ballot(l.fidx >= 0);
+  const int rl = l.fidx < 0 ? -1 : __popcll(extended & ((1ull << l.lane) - 1));
+  const int sw = P::state(mf);
+  auto length = [&](int c) { return min(seg, T - (nseg - 1 - c) * seg); };  // of the c-th segment
+  auto time_of = [&](int c, int i) { return (nseg - 1 - c) * seg + length(c) - 1 - i; };
+  // step i (counted from its end) of the c-th segment
+  auto get = [&](int c, int i, State<S, FREE>& st) {
+    if (!act) return;
+    if constexpr (NR > 0) get_slot(st, ring + (size_t)((c % 3) * seg + length(c) - 1 - i) * sw, kWave, mf, l.lane, rl);
+    else get_slot(st, A.ck + (size_t)time_of(c, i) * RW, ns, nf, l.slot, l.fidx);
+  };
+  constexpr bool CTL3 = BALL;
+  if (NR > 0 && wid < NR) {
+    const LinkC<S> L = load_linkc<S, FR>(A.P, l);
+    State<S, FREE> st = {};
+    for (int k = 0; k <= phases; ++k) {
+      const int c = k / ppseg, part = k % ppseg;
+      if (c < nseg) {
+        const int n = length(c), share = (seg - 1 + ppseg - 1) / ppseg, t0 = (nseg - 1 - c) * seg;
+        S* const base = ring + (size_t)(c % 3) * seg * sw;
+        if (part == 0 && act) {
+          get_slot(st, A.ck + (size_t)(nseg - 1 - c) * RW, ns, nf, l.slot, l.fidx);
+          put_slot(st, base, kWave, mf, l.lane, rl);
+        }
+        for (int j = part * share + 1; j <= min((part + 1) * share, n - 1); ++j) {
+          const V3<S> tau = act ? load_ctl<CTL3>(A.tau + (size_t)(t0 + j - 1) * nu, l) : zero3<S>();
+          advance<FR, false, false>(A.P, gravity(A.P), l, L, st, tau, A.dt, maxd, xreplay);
+          if (act) put_slot(st, base + (size_t)j * sw, kWave, mf, l.lane, rl);
+        }
+      }
+      __syncthreads();
+    }
+  } else if (wid < NR + NP) {
+    const int j = wid - NR;
+    double* const xb = xbs + j * P::rec;
+    const FrameLane<S> p = frame_lane<S, FR>(A.P, l, maxd);
+    State<S, FREE> nxt = {};
+    V3<S> nt = zero3<S>();
+    auto fetch = [&](int k) {  // phase k's step, if it has one
+      const int c = (k - ahead) / ppseg, i = (k - ahead) % ppseg * NP + j;
+      if (k < ahead || c >= nseg || i >= length(c)) return;
+      if constexpr (NR == 0) get(c, i, nxt);
+      if (act) nt = load_ctl<CTL3>(A.tau + (size_t)time_of(c, i) * nu, l);
+    };
+    fetch(ahead);
+    for (int k = 0; k <= phases; ++k) {
+      const int c = (k - ahead) / ppseg, i = (k - ahead) % ppseg * NP + j;
+      if (k >= ahead && c < nseg && i < length(c)) {
+        if constexpr (NR > 0) get(c, i, nxt);
+        const State<double, FREE> st = cvt_state<double>(nxt);
+        const V3<double> tau = cvt3<double>(nt);
+        fetch(k + 1);
+        FrameStep o = frame_recompute<FREE, BALL>(p, st, limit_tau<FR>(A.P, l, st, tau), xb);
+        double* const tp = tape + ((k & 1) * NP + j) * P::TW;
+        frame_fields<FREE, BALL>(o, [&](int f, double& v) { tp[f * kWave + l.lane] = v; });
+      } else if (k >= ahead) {
+        fetch(k + 1);
+      }
+      __syncthreads();
+    }
+  } else {
+    double* const xb = xbs + NP * P::rec;
+    const FrameLane<S> p = frame_lane<S, FR>(A.P, l, maxd);
+    const double dt = double(A.dt);
+    int nonfin = 0;
+    State<double, FREE> x1 = seed_state<S, double, FREE>(A, l);
+    State<S, FREE> nxt = {};
+    if constexpr (FREE && NR == 0) get(0, 0, nxt);
+    for (int k = 0; k <= phases; ++k) {
+      const int c = k > ahead ? (k - 1 - ahead) / ppseg : nseg, i0 = (k - 1 - ahead) % ppseg * NP;
+      for (int j = 0; j < NP && c < nseg && i0 + j < length(c); ++j) {
+        const int i = i0 + j;
+        FrameStep o;
+        const double* tp = tape + (((k - 1) & 1) * NP + j) * P::TW;
+        frame_fields<FREE, BALL>(o, [&](int f, double& v) { v = tp[f * kWave + l.lane]; });
+        State<double, FREE> st = {};
+        if constexpr (FREE) {
+          if constexpr (NR > 0) get(c, i, nxt);
+          st = cvt_state<double>(nxt);
+          if (NR == 0 && i + 1 < T) get(0, i + 1, nxt);
+        } else {
+          st.q[0] = o.q;
+          st.qd[0] = o.qd;
+        }
+        double lq, lqd;
+        limit_slopes<FR>(A.P, l, st, lq, lqd);
+        const V3<double> taub = frame_reverse<FREE, BALL>(p, o, st, dt, lq, lqd, x1, xb);
+        frame_outputs<S, FREE>(A, l, time_of(c, i), taub, x1, nonfin);
+      }
+      __syncthreads();
+    }
+    if (act) {
+      const State<S, FREE> x0 = cvt_state<S>(x1);
+      store_state(x0, l, A.gq0, A.gqd0);
+      nonfin += nonfinite_state(x0, l);
+    }
+    report_nonfinite(A.P.status, nonfin);
+  }
+}
+
 }  // namespace
 
 }  // namespace aba

@@ -103,3 +103,22 @@ def test_a_diverged_system_leaves_its_neighbours_alone(dtype, name, bad):
         keep = np.r_[0:o[bad], o[bad + 1]:o[-1]]
         assert np.array_equal(a[..., keep], r[..., keep])
         assert not np.isfinite(a[..., o[bad]:o[bad + 1]]).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("name", ["turned_4_5_17", "limits", "roots", "balls"])
+@pytest.mark.parametrize("T,K", [(1, 1), (2, 1), (9, 1), (9, 4), (12, 4), (3, 4), (9, 2), (9, 40)])
+def test_pipelined_wavefronts_agree_with_one(dtype, name, T, K):
+    """The pipelined kernels (one batch per workgroup) at horizons around their
+    phases and segments, with more systems than one wavefront holds, against
+    the one-wavefront kernel at K = 1: the same arithmetic, so the same
+    gradients up to how the compiler contracts it, in FP64 round-off (1e-13 of
+    the largest link count cubed, as above)."""
+    draws = [(s, q, v, np.resize(u, (T, u.shape[1]))) for s, q, v, u in DRAWS[name]] * 5
+    b = synth.make_batch(draws, 1e-3)
+    print("case", dtype, name, T, K, flush=True)
+    got, _ = run(b, K, dtype)
+    ref, _ = run(b, 1, dtype, (1, 1, False))
+    tol = 1e-13 * 17 ** 3 if dtype is torch.float64 else 1e-6
+    for a, r in zip(got, ref):
+        assert rel(a, r, 1e-12) < tol
