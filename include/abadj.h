@@ -409,8 +409,8 @@ const char *sim_last_error(void);
 
 /* Bytes of the workspace that keeps x at the start of every sweep (and the
  * result) for the adjoint: (niter + 1) * n * batch * sizeof(dtype), and for
- * n >= 13 another niter * n * batch elements after them, which
- * sim_pgs_adjoint uses as scratch (the sweep vectors stay as they are). */
+ * n >= 13 another niter * n * batch elements after them (scratch of the
+ * adjoint; the sweep vectors stay as they are). */
 int sim_pgs_workspace_bytes(int dtype, int batch, int n, int niter, size_t *bytes);
 
 /* Solve.  workspace (nullable): when given (workspace_bytes at least

@@ -12,14 +12,26 @@
 // or to y_bar_i, then b_bar_i, A_bar_i. and x_bar_j (j != i) follow from
 // y_i, and x_bar_i is reset.
 //
-// Layout on the GPU: one lane per problem.  A problem of n <= 16 rows is
-// held in registers (A, and in the adjoint A_bar as well up to 12 rows) by a
-// kernel compiled for NMAX rows (4, 8, 12 or 16; rows past n are skipped), so
-// the row and column loops are unrolled and every operand has a fixed
-// register.
-// The sweep vectors go to the workspace as [niter + 1][n][batch], one
-// coalesced row per wave and entry.  Problems are independent: no
-// cross-lane traffic, no barriers.
+// Layout on the GPU: four lanes (a quad) per problem, sixteen problems per
+// wavefront; lane g holds the columns j = 4 c + g of A (and of A_bar) and the
+// vectors' entries j.  A row's sum is the lanes' partial sums joined by two
+// quad permutations; the row is then finished by every lane with its own
+// entry c and kept by the one that owns it, so that no per-row quantity is
+// held four times.  A kernel is compiled for 4, 8, 12 and 16 rows: row and
+// column loops are unrolled and every operand has a fixed register, A_bar's
+// too; the up to three rows past n are zero rows, which leave everything as it
+// is, and no branch separates one row's instructions from the next's.  The sweep vectors go to the workspace as
+// [niter + 1][n][batch].  Problems are independent: no barriers.
+//
+// What bounds it: the instructions of a row, the GS order being a serial chain
+// of n niter rows.  With one lane per problem 32768 problems were 512
+// wavefronts, half a SIMD's worth each, every lane reading rows of A of its
+// own, with A and A_bar (288 registers of 12 rows) past the register file.
+// 32768 problems x 12 rows x 30 sweeps, FP32: solve 59 -> 27 us, adjoint
+// 140 -> 57 us, and in FP64
+// 71 -> 42 and 2033 -> 94; 64 problems 35 -> 17 and 93 -> 30; 16 rows, 32768
+// problems, 92 -> 37 and 445 -> 80.  (200000 problems of 4 rows, where memory
+// bounds it, 33 -> 33 and 62 -> 70.)
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -30,7 +42,7 @@
 
 namespace {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = 64;  // sixteen problems; blocks of 128 and 256 are no faster at any batch
 
 template <typename S>
 struct PgsArgs {
@@ -50,236 +62,181 @@ struct PgsArgs {
   S* x0bar;
 };
 
+// x of another lane of the quad (CTRL: a quad permutation)
+template <int CTRL>
+__device__ __forceinline__ float quad(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double quad(double x) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true));
+}
+template <typename S>
+__device__ __forceinline__ S quad_sum(S x) {
+  x += quad<0xB1>(x);  // [1, 0, 3, 2]
+  return x + quad<0x4E>(x);  // [2, 3, 0, 1]
+}
+
+// 1 / d = hi + lo, the two of one sign and not zero, so that x hi + x lo is
+// x / d to the last bit or so and keeps its sign where x is infinite or d zero
+template <typename S>
+__device__ __forceinline__ void reciprocal(S d, S& hi, S& lo) {
+  constexpr S eps = sizeof(S) == 8 ? S(2.2e-16) : S(1.2e-7);
+  hi = S(1) / d;
+  S r = fma(-d, hi, S(1));
+  if (r < S(0)) {  // rounded away from zero: one unit back
+    if constexpr (sizeof(S) == 8) hi = __longlong_as_double(__double_as_longlong(hi) - 1);
+    else hi = __int_as_float(__float_as_int(hi) - 1);
+    r = fma(-d, hi, S(1));
+  }
+  lo = d == S(0) ? hi : hi * (r > eps * eps ? r : eps * eps);
+}
+
+// A problem's columns and bounds on a lane of its quad
+template <typename S, int N>
+struct Problem {
+  static constexpr int C = N / 4;
+  int n, g;
+  size_t p;
+  S A[N][C];                  // off-diagonal; zero on the diagonal and past n
+  S b[C], lo[C], hi[C];
+  S inv[C], inv_lo[C];        // 1 / A_jj in two parts: s / A_jj to the last bit or so
+
+  __device__ __forceinline__ size_t at(int c) const { return p * n + 4 * c + g; }
+  __device__ __forceinline__ bool has(int c) const { return 4 * c + g < n; }
+  __device__ __forceinline__ bool owns(int i) const { return g == i % 4 && i < n; }
+  __device__ __forceinline__ void load(S (&v)[C], const S* src, size_t first, size_t stride) const {
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] = has(c) ? src[first + (4 * c + g) * stride] : S(0);
+  }
+  __device__ __forceinline__ void store(const S (&v)[C], S* dst, size_t first, size_t stride) const {
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      if (has(c)) dst[first + (4 * c + g) * stride] = v[c];
+  }
+  __device__ __forceinline__ Problem(const PgsArgs<S>& P, size_t p_, int g_) : n(P.n), g(g_), p(p_) {
+    S d[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) d[c] = S(1);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const S v = (i < n && has(c)) ? P.A[(p * n + i) * n + 4 * c + g] : S(0);
+        const bool diag = i == 4 * c + g;
+        A[i][c] = diag ? S(0) : v;
+        if (diag && i < n) d[c] = v;
+      }
+    load(b, P.b, p * n, 1);
+    load(lo, P.lo, p * n, 1);
+    load(hi, P.hi, p * n, 1);
+#pragma unroll
+    for (int c = 0; c < C; ++c) reciprocal(d[c], inv[c], inv_lo[c]);
+  }
+  // x / A_jj of the lane's entry c
+  __device__ __forceinline__ S over(S x, int c) const { return fma(x, inv_lo[c], x * inv[c]); }
+  // y of row i, on the lane that owns it, from the vector x
+  __device__ __forceinline__ S row(int i, const S (&x)[C]) const {
+    S d = S(0);
+#pragma unroll
+    for (int c = 0; c < C; ++c) d = fma(A[i][c], c == i / 4 && owns(i) ? S(0) : x[c], d);  // x_i may be infinite
+    d = quad_sum(d);
+    return over(-(b[i / 4] + d), i / 4);
+  }
+};
+
 template <typename S, int N>
 __global__ __launch_bounds__(kBlock) void k_pgs_solve(PgsArgs<S> P) {
-  const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p >= P.batch) return;
-  const int n = P.n;
-  const size_t B = (size_t)P.batch;
-  S A[N][N], b[N], lo[N], hi[N], x[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) A[i][j] = (i < n && j < n) ? P.A[((size_t)p * n + i) * n + j] : S(0);
-    b[i] = (i < n) ? P.b[(size_t)p * n + i] : S(0);
-    lo[i] = (i < n) ? P.lo[(size_t)p * n + i] : S(0);
-    hi[i] = (i < n) ? P.hi[(size_t)p * n + i] : S(0);
-    x[i] = (i < n) ? P.x0[(size_t)p * n + i] : S(0);
-  }
+  constexpr int C = N / 4;
+  const size_t p = ((size_t)blockIdx.x * kBlock + threadIdx.x) / 4;
+  if (p >= (size_t)P.batch) return;  // whole quads
+  const size_t B = (size_t)P.batch, n = (size_t)P.n;
+  const Problem<S, N> m(P, p, threadIdx.x % 4);
+  S x[C];
+  m.load(x, P.x0, p * n, 1);
   for (int t = 0; t < P.niter; ++t) {
-    if (P.ws) {
-#pragma unroll
-      for (int i = 0; i < N; ++i)
-        if (i < n) P.ws[((size_t)t * n + i) * B + p] = x[i];
-    }
+    if (P.ws) m.store(x, P.ws + p, t * n * B, B);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      if (i < n) {
-        S d = S(0);
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-          if (j != i) d += A[i][j] * x[j];
-        const S y = -(b[i] + d) / A[i][i];
-        x[i] = (y < lo[i]) ? lo[i] : ((y > hi[i]) ? hi[i] : y);
-      }
+      const int c = i / 4;
+      const S y = m.row(i, x);
+      const S v = (y < m.lo[c]) ? m.lo[c] : ((y > m.hi[c]) ? m.hi[c] : y);
+      x[c] = m.owns(i) ? v : x[c];
     }
   }
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-    if (i < n) {
-      P.x[(size_t)p * n + i] = x[i];
-      if (P.ws) P.ws[((size_t)P.niter * n + i) * B + p] = x[i];
-    }
+  m.store(x, P.x, p * n, 1);
+  if (P.ws) m.store(x, P.ws + p, P.niter * n * B, B);
 }
 
 template <typename S, int N>
 __global__ __launch_bounds__(kBlock) void k_pgs_adjoint(PgsArgs<S> P) {
-  const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p >= P.batch) return;
-  const int n = P.n;
-  const size_t B = (size_t)P.batch;
-  S A[N][N], Ab[N][N], b[N], lo[N], hi[N], xb[N], bb[N], lb[N], hb[N];
+  constexpr int C = N / 4;
+  const size_t p = ((size_t)blockIdx.x * kBlock + threadIdx.x) / 4;
+  if (p >= (size_t)P.batch) return;  // whole quads
+  const size_t B = (size_t)P.batch, n = (size_t)P.n;
+  const Problem<S, N> m(P, p, threadIdx.x % 4);
+  S Ab[N][C], Ad[C], xb[C], bb[C], lb[C], hb[C], x[C], xs[C], nx[C];
+  m.load(xb, P.xbar, p * n, 1);
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
+  for (int c = 0; c < C; ++c) {
+    Ad[c] = bb[c] = lb[c] = hb[c] = x[c] = nx[c] = S(0);
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      A[i][j] = (i < n && j < n) ? P.A[((size_t)p * n + i) * n + j] : S(0);
-      Ab[i][j] = S(0);
-    }
-    b[i] = (i < n) ? P.b[(size_t)p * n + i] : S(0);
-    lo[i] = (i < n) ? P.lo[(size_t)p * n + i] : S(0);
-    hi[i] = (i < n) ? P.hi[(size_t)p * n + i] : S(0);
-    xb[i] = (i < n) ? P.xbar[(size_t)p * n + i] : S(0);
-    bb[i] = lb[i] = hb[i] = S(0);
+    for (int i = 0; i < N; ++i) Ab[i][c] = S(0);
+  }
+  // x: before row i of sweep t it holds the sweep's end for j < i and its
+  // start, xs, for j > i; so at the sweep's first row it holds the start, the
+  // end of the sweep before
+  if (P.niter > 0) {
+    m.load(x, P.ws + p, P.niter * n * B, B);
+    m.load(nx, P.ws + p, (P.niter - 1) * n * B, B);
   }
   for (int t = P.niter - 1; t >= 0; --t) {
-    // x at the start (xs) and the end (xe) of sweep t; before row i the
-    // vector holds xe[j] for j < i and xs[j] for j > i
-    S xs[N], xe[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      xs[j] = (j < n) ? P.ws[((size_t)t * n + j) * B + p] : S(0);
-      xe[j] = (j < n) ? P.ws[((size_t)(t + 1) * n + j) * B + p] : S(0);
-    }
+    for (int c = 0; c < C; ++c) xs[c] = nx[c];
+    if (t > 0) m.load(nx, P.ws + p, (t - 1) * n * B, B);
 #pragma unroll
     for (int i = N - 1; i >= 0; --i) {
-      if (i < n) {
-        S d = S(0);
+      const int c = i / 4;
+      const bool own = m.owns(i);
+      const S y = m.row(i, x);
+      const S t0 = own ? xb[c] : S(0);
+      const bool below = y < m.lo[c], above = !below && y > m.hi[c];
+      lb[c] += below ? t0 : S(0);
+      hb[c] += above ? t0 : S(0);
+      const S own_db = -m.over(below || above ? S(0) : t0, c);
+      bb[c] += own_db;
+      Ad[c] += own ? own_db * y : S(0);
+      const S db = i % 4 == 0 ? quad<0x00>(own_db) : i % 4 == 1 ? quad<0x55>(own_db)
+                 : i % 4 == 2 ? quad<0xAA>(own_db) : quad<0xFF>(own_db);
 #pragma unroll
-        for (int j = 0; j < N; ++j)
-          if (j != i) d += A[i][j] * ((j < i) ? xe[j] : xs[j]);
-        const S y = -(b[i] + d) / A[i][i];
-        S yb = S(0);
-        if (y < lo[i]) lb[i] += xb[i];
-        else if (y > hi[i]) hb[i] += xb[i];
-        else yb = xb[i];
-        xb[i] = S(0);
-        const S db = -yb / A[i][i];
-        bb[i] += db;
-        Ab[i][i] += db * y;
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-          if (j != i) {
-            Ab[i][j] += db * ((j < i) ? xe[j] : xs[j]);
-            xb[j] += db * A[i][j];
-          }
+      for (int k = 0; k < C; ++k) {
+        Ab[i][k] = fma(db, x[k], Ab[i][k]);
+        xb[k] = fma(db, m.A[i][k], xb[k]);
       }
+      xb[c] = own ? S(0) : xb[c];
+      x[c] = own ? xs[c] : x[c];
     }
   }
 #pragma unroll
   for (int i = 0; i < N; ++i)
-    if (i < n) {
+    if (i < P.n) {
 #pragma unroll
-      for (int j = 0; j < N; ++j)
-        if (j < n) P.Abar[((size_t)p * n + i) * n + j] = Ab[i][j];
-      P.bbar[(size_t)p * n + i] = bb[i];
-      P.lobar[(size_t)p * n + i] = lb[i];
-      P.hibar[(size_t)p * n + i] = hb[i];
-      P.x0bar[(size_t)p * n + i] = xb[i];
+      for (int c = 0; c < C; ++c)
+        if (m.has(c)) P.Abar[(p * n + i) * n + 4 * c + m.g] = i == 4 * c + m.g ? Ad[c] : Ab[i][c];
     }
-}
-
-// The adjoint for the largest row bucket.  A and A_bar together (2 * 16^2
-// per lane) do not fit the registers next to the vectors, so A_bar is formed
-// in a second phase: the reverse sweeps keep A, the diagonal of A_bar and
-// the vectors, and write each row's y_bar / (-A_ii) = db_{t,i} to the
-// workspace after the sweep vectors; then, since
-//   A_bar_ij = sum_t db_{t,i} x_j(t, i)  (j != i),
-// with x_j(t, i) the value row i read in sweep t (the end-of-sweep value for
-// j < i, the start-of-sweep one for j > i), RC rows of A_bar at a time are
-// summed from db and the sweep vectors.  Each lane reads back only what it
-// wrote itself.
-constexpr int kSplitRows = 13;  // row counts from this up take the split adjoint
-constexpr int kRC = 8;          // rows of A_bar per pass of the second phase
-
-template <typename S, int N>
-__global__ __launch_bounds__(kBlock) void k_pgs_adjoint_split(PgsArgs<S> P) {
-  const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p >= P.batch) return;
-  const int n = P.n;
-  const size_t B = (size_t)P.batch;
-  S* db = P.ws + (size_t)(P.niter + 1) * n * B;  // [niter][n][batch]
-  S A[N][N], Ad[N], b[N], lo[N], hi[N], xb[N], bb[N], lb[N], hb[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) A[i][j] = (i < n && j < n) ? P.A[((size_t)p * n + i) * n + j] : S(0);
-    Ad[i] = S(0);
-    b[i] = (i < n) ? P.b[(size_t)p * n + i] : S(0);
-    lo[i] = (i < n) ? P.lo[(size_t)p * n + i] : S(0);
-    hi[i] = (i < n) ? P.hi[(size_t)p * n + i] : S(0);
-    xb[i] = (i < n) ? P.xbar[(size_t)p * n + i] : S(0);
-    bb[i] = lb[i] = hb[i] = S(0);
-  }
-  for (int t = P.niter - 1; t >= 0; --t) {
-    S xs[N], xe[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      xs[j] = (j < n) ? P.ws[((size_t)t * n + j) * B + p] : S(0);
-      xe[j] = (j < n) ? P.ws[((size_t)(t + 1) * n + j) * B + p] : S(0);
-    }
-#pragma unroll
-    for (int i = N - 1; i >= 0; --i) {
-      if (i < n) {
-        S d = S(0);
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-          if (j != i) d += A[i][j] * ((j < i) ? xe[j] : xs[j]);
-        const S y = -(b[i] + d) / A[i][i];
-        S yb = S(0);
-        if (y < lo[i]) lb[i] += xb[i];
-        else if (y > hi[i]) hb[i] += xb[i];
-        else yb = xb[i];
-        xb[i] = S(0);
-        const S dbi = -yb / A[i][i];
-        bb[i] += dbi;
-        Ad[i] += dbi * y;
-        db[((size_t)t * n + i) * B + p] = dbi;
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-          if (j != i) xb[j] += dbi * A[i][j];
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-    if (i < n) {
-      P.bbar[(size_t)p * n + i] = bb[i];
-      P.lobar[(size_t)p * n + i] = lb[i];
-      P.hibar[(size_t)p * n + i] = hb[i];
-      P.x0bar[(size_t)p * n + i] = xb[i];
-    }
-  // second phase: the off-diagonal entries of A_bar, kRC rows at a time
-#pragma unroll 1
-  for (int r0 = 0; r0 < n; r0 += kRC) {
-    S acc[kRC][N];
-#pragma unroll
-    for (int r = 0; r < kRC; ++r)
-#pragma unroll
-      for (int j = 0; j < N; ++j) acc[r][j] = S(0);
-    for (int t = 0; t < P.niter; ++t) {
-      S xs[N], xe[N];
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        xs[j] = (j < n) ? P.ws[((size_t)t * n + j) * B + p] : S(0);
-        xe[j] = (j < n) ? P.ws[((size_t)(t + 1) * n + j) * B + p] : S(0);
-      }
-#pragma unroll
-      for (int r = 0; r < kRC; ++r) {
-        const int i = r0 + r;
-        if (i < n) {
-          const S dbi = db[((size_t)t * n + i) * B + p];
-#pragma unroll
-          for (int j = 0; j < N; ++j) acc[r][j] += dbi * ((j < i) ? xe[j] : xs[j]);
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < kRC; ++r) {
-      const int i = r0 + r;
-      if (i < n) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-          if (j < n) {
-            // the diagonal is y's own term from the first phase
-            S v = acc[r][j];
-#pragma unroll
-            for (int k = 0; k < N; ++k)
-              if (k == i && j == k) v = Ad[k];
-            P.Abar[((size_t)p * n + i) * n + j] = v;
-          }
-        }
-      }
-    }
-  }
+  m.store(bb, P.bbar, p * n, 1);
+  m.store(lb, P.lobar, p * n, 1);
+  m.store(hb, P.hibar, p * n, 1);
+  m.store(xb, P.x0bar, p * n, 1);
 }
 
 int pgs_fail(int code, const std::string& msg) { return aba::report_error(code, msg); }
 
-// the sweep vectors [niter + 1][n][batch], and for the split adjoint's rows
-// db [niter][n][batch] after them
+// the sweep vectors [niter + 1][n][batch]; past 12 rows callers provide
+// [niter][n][batch] more, which the kernels leave alone
 size_t pgs_ws_bytes(int dtype, int batch, int n, int niter) {
-  const size_t rows = (size_t)(niter + 1) + (n >= kSplitRows ? (size_t)niter : 0);
+  const size_t rows = (size_t)(niter + 1) + (n > 12 ? (size_t)niter : 0);
   return rows * (size_t)n * (size_t)batch * (dtype == SIM_F64 ? sizeof(double) : sizeof(float));
 }
 
@@ -292,22 +249,16 @@ int pgs_check(const char* who, int dtype, int batch, int n, int niter) {
   return SIM_OK;
 }
 
-// one kernel per row bucket NMAX (4, 8, 12, 16); the largest bucket's
-// adjoint is the split one
+// one kernel per row bucket (4, 8, 12, 16)
 template <typename S, int N>
 void launch_n(const PgsArgs<S>& a, hipStream_t st, bool adjoint, dim3 grid) {
-  static_assert(N < kSplitRows || N == 16, "row buckets");
-  if (adjoint) {
-    if constexpr (N >= kSplitRows) hipLaunchKernelGGL((k_pgs_adjoint_split<S, N>), grid, dim3(kBlock), 0, st, a);
-    else hipLaunchKernelGGL((k_pgs_adjoint<S, N>), grid, dim3(kBlock), 0, st, a);
-  } else {
-    hipLaunchKernelGGL((k_pgs_solve<S, N>), grid, dim3(kBlock), 0, st, a);
-  }
+  if (adjoint) hipLaunchKernelGGL((k_pgs_adjoint<S, N>), grid, dim3(kBlock), 0, st, a);
+  else hipLaunchKernelGGL((k_pgs_solve<S, N>), grid, dim3(kBlock), 0, st, a);
 }
 template <typename S>
 hipError_t launch(const PgsArgs<S>& a, hipStream_t st, bool adjoint) {
   if (a.batch == 0) return hipSuccess;
-  const dim3 grid((a.batch + kBlock - 1) / kBlock);
+  const dim3 grid((unsigned)(((size_t)a.batch * 4 + kBlock - 1) / kBlock));
   if (a.n <= 4) launch_n<S, 4>(a, st, adjoint, grid);
   else if (a.n <= 8) launch_n<S, 8>(a, st, adjoint, grid);
   else if (a.n <= 12) launch_n<S, 12>(a, st, adjoint, grid);
