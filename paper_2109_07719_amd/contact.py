@@ -17,6 +17,7 @@ import numpy as np
 import torch
 
 from . import _native as N
+from .sim import _ptr, _stream
 
 _DT = {torch.float32: N.SIM_F32, torch.float64: N.SIM_F64}
 
@@ -41,10 +42,6 @@ def pack_params(system, centers, radii) -> np.ndarray:
                             [system.mass[i]], system.com[i], system.Ic[i]]) for i in range(system.n)]
     rows += [np.concatenate([np.asarray(c, np.float64).reshape(3), [r]]) for c, r in zip(centers, radii)]
     return np.concatenate(rows) if rows else np.zeros(0)
-
-
-def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
 
 
 class ContactBatch:
@@ -111,7 +108,7 @@ class ContactBatch:
         chosen, rms, gms = _Tiling(), ctypes.c_double(), ctypes.c_double()
         N.check(N.lib().sim_contact_autotune(ctypes.byref(self.m), _DT[self.dtype], self.B, _ptr(self.P), _ptr(q0),
                                              _ptr(qd0), _ptr(tau), float(dt), T,
-                                             ctypes.c_void_p(torch.cuda.current_stream().cuda_stream),
+                                             _stream(),
                                              ctypes.byref(chosen), ctypes.byref(rms), ctypes.byref(gms)))
         self.set_tiling(chosen.rollout_systems_per_wave, chosen.grad_systems_per_wave, chosen.grad_lds)
         return dict(self.tiling, rollout_ms_per_probe_step=rms.value, grad_ms_per_probe_step=gms.value)
@@ -132,7 +129,7 @@ class ContactBatch:
         nc = torch.empty((T, self.B), dtype=torch.int32, device=q0.device) if counts else None
         N.check(N.lib().sim_contact_rollout(ctypes.byref(self.m), _DT[self.dtype], self.B, _ptr(self.P), _ptr(q0),
                                             _ptr(qd0), _ptr(tau), float(dt), T, _ptr(tr), _ptr(qT), _ptr(qdT),
-                                            _ptr(nc), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
+                                            _ptr(nc), _stream()))
         out = (qT, qdT)
         if traj:
             out += (tr,)
@@ -154,5 +151,5 @@ class ContactBatch:
         N.check(N.lib().sim_contact_rollout_grad(ctypes.byref(self.m), _DT[self.dtype], self.B, _ptr(self.P),
                                                  _ptr(traj), _ptr(tau), float(dt), T, _ptr(gqT), _ptr(gqdT),
                                                  _ptr(gq0), _ptr(gqd0), _ptr(gtau), _ptr(gmu),
-                                                 ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
+                                                 _stream()))
         return (gq0, gqd0, gtau, gmu) if mu_grad else (gq0, gqd0, gtau)

@@ -18,14 +18,13 @@ forward mode, function transforms, tracing) runs the torch expressions.
 """
 from __future__ import annotations
 
-import ctypes
-
 import numpy as np
 import torch
 import torch.autograd.forward_ad as fwad
 from torch.utils._python_dispatch import _get_current_dispatch_mode
 
 from . import _native as N
+from .sim import _ptr, _stream
 
 _DT = {torch.float32: N.SIM_F32, torch.float64: N.SIM_F64}
 _MAX_PATH = 64   # one lane per link of a path
@@ -159,12 +158,11 @@ class LinkPoints(torch.nn.Module):
                 and fits(self.pts, 3 * self._path.shape[0]) and self.pts.dim() == 2)
 
     def _call(self, name, q, ETt, rT, ax, pts, *last):
-        p = lambda t: ctypes.c_void_p(t.data_ptr())
+        p = _ptr
         with torch.cuda.device(q.device):
-            stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
             N.check(getattr(N.lib(), name)(_DT[q.dtype], self._path.shape[0], self._path.shape[1], p(self._path),
                                            p(self._jtype), p(self.qidx), p(ETt), p(rT), p(ax), p(pts), p(q),
-                                           *(p(t) for t in last), stream))
+                                           *(p(t) for t in last), _stream()))
 
     def forward(self, q):
         return _Points.apply(q, self) if self._native(q) else self._positions(q)
