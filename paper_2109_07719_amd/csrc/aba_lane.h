@@ -197,10 +197,13 @@ ABA_HD V6<S> p3_accel(const LinkC<S>& L, Tape<S>& t, const V6<S>& apar) {
 }
 
 // ------------------------------------------------------- free-floating root
-// 6x6 SPD factorisation (lower Cholesky, packed rows)
+// 6x6 SPD factorisation (lower Cholesky, packed rows, the diagonal as its
+// reciprocal: six divisions in place of 27, a tenth of a quadruped's forward
+// step)
 template <typename S>
 struct Chol6 {
-  S L[21];
+  S L[21];  // the diagonal is not set
+  S inv[6];
 };
 template <typename S>
 ABA_HD void sysp_dense(const SySp<S>& M, S A[36]) {
@@ -228,9 +231,9 @@ ABA_HD Chol6<S> chol6(const SySp<S>& M) {
 #pragma unroll
       for (int k = 0; k < j; ++k) s = s - f.L[i * (i + 1) / 2 + k] * f.L[j * (j + 1) / 2 + k];
       if (i == j)
-        f.L[i * (i + 1) / 2 + i] = sqrt(s);
+        f.inv[i] = S(1) / sqrt(s);
       else
-        f.L[i * (i + 1) / 2 + j] = s / f.L[j * (j + 1) / 2 + j];
+        f.L[i * (i + 1) / 2 + j] = s * f.inv[j];
     }
   }
   return f;
@@ -243,14 +246,14 @@ ABA_HD V6<S> chol6_solve(const Chol6<S>& f, const V6<S>& b) {
     S s = x[i];
 #pragma unroll
     for (int k = 0; k < i; ++k) s = s - f.L[i * (i + 1) / 2 + k] * x[k];
-    x[i] = s / f.L[i * (i + 1) / 2 + i];
+    x[i] = s * f.inv[i];
   }
 #pragma unroll
   for (int i = 5; i >= 0; --i) {
     S s = x[i];
 #pragma unroll
     for (int k = i + 1; k < 6; ++k) s = s - f.L[k * (k + 1) / 2 + i] * x[k];
-    x[i] = s / f.L[i * (i + 1) / 2 + i];
+    x[i] = s * f.inv[i];
   }
   return v6<S>(v3<S>(x[0], x[1], x[2]), v3<S>(x[3], x[4], x[5]));
 }
