@@ -1,4 +1,5 @@
-// The FP64 adjoint of trees, free roots, prismatic and ball joints and joint
+// The FP64 adjoint (and an FP64 handle's forward step: frame_recompute alone)
+// of trees, free roots, prismatic and ball joints and joint
 // limits, in the base frame, by the adjoint of the inverse dynamics: with w =
 // M^-1 (dt qd1_bar) (two sweeps with the step's articulated factors),
 //   tau_bar = w,  (q_bar, qd_bar) -= d/d(q, qd) <w, ID(q, qd, qdd)> at fixed qdd
@@ -164,9 +165,10 @@ __device__ __forceinline__ V6<double> from_point(const V3<double>& n, const V3<d
   return v6<double>(n + cross(o, f), f);
 }
 
+// acc: the 1-dof joint's acceleration
 template <bool FREE, bool BALL, typename S>
 __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, const State<double, FREE>& st,
-                                                     const V3<double>& ctl, double* xb) {
+                                                     const V3<double>& ctl, double* xb, double* acc = nullptr) {
   FrameStep o;
   const V3<double> z3 = zero3<double>();
   o.q = st.q[0];
@@ -353,6 +355,7 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
   }
   o.F = mul(IA, a) + F;
   o.Ap = ap + A0 - cb;
+  if (acc != nullptr) *acc = qdd;
   if constexpr (FREE) {
     if (p.root) root_pack(o, f);
   }
@@ -650,7 +653,7 @@ __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(Bw
   };
   constexpr bool CTL3 = BALL;
   if (NR > 0 && wid < NR) {
-    const LinkC<S> L = load_linkc<S, FR>(A.P, l);
+    const auto SC = step_const<false, kFrameStep<false, S>, FR>(A.P, l, load_linkc<S, FR>(A.P, l), maxd);
     State<S, FREE> st = {};
     for (int k = 0; k <= phases; ++k) {
       const int c = k / ppseg, part = k % ppseg;
@@ -663,7 +666,7 @@ __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(Bw
         }
         for (int j = part * share + 1; j <= min((part + 1) * share, n - 1); ++j) {
           const V3<S> tau = act ? load_ctl<CTL3>(A.tau + (size_t)(t0 + j - 1) * nu, l) : zero3<S>();
-          advance<FR, false, false>(A.P, gravity(A.P), l, L, st, tau, A.dt, maxd, xreplay);
+          advance<FR, false, false>(A.P, gravity(A.P), l, SC, st, tau, A.dt, maxd, xreplay);
           if (act) put_slot(st, base + (size_t)j * sw, kWave, mf, l.lane, rl);
         }
       }

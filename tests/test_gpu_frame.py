@@ -122,3 +122,27 @@ def test_pipelined_wavefronts_agree_with_one(dtype, name, T, K):
     tol = 1e-13 * 17 ** 3 if dtype is torch.float64 else 1e-6
     for a, r in zip(got, ref):
         assert rel(a, r, 1e-12) < tol
+
+
+@pytest.mark.parametrize("name", list(DRAWS))
+def test_base_frame_forward_fp64(name):
+    """The FP64 handles' forward step, in the base frame: end state and
+    trajectory."""
+    from paper_2109_07719_amd.sim import Sim
+    b = synth.make_batch(DRAWS[name], 1e-3)
+    print("case", name, flush=True)
+    sim = Sim(b.systems, (1.0, -9.0, 2.0), dtype=torch.float64)
+    f = lambda x: torch.tensor(np.ascontiguousarray(x), device="cuda")
+    qT, qdT, tr = sim.forward(f(b.q0), f(b.qd0), f(b.tau), b.dt, K=0, traj=True)
+    q1, qd1, _ = sim.forward(f(b.q0), f(b.qd0), f(b.tau[:1]), b.dt, K=0)
+    oq, ov, ou = b.offsets()
+    for k, s in enumerate(b.systems):
+        m = O.Model(s, (1.0, -9.0, 2.0))
+        q, v, u = slice(oq[k], oq[k + 1]), slice(ov[k], ov[k + 1]), slice(ou[k], ou[k + 1])
+        tol = 1e-13 * max(s.n, 4) ** 3
+        for a, r in zip((qT[q], qdT[v]), O.rollout(m, b.q0[q], b.qd0[v], b.tau[:, u], b.dt)):
+            assert rel(a.cpu().numpy(), r, 1e-12) < tol, (k, s.n)
+        for a, r in zip((q1[q], qd1[v]), O.rollout(m, b.q0[q], b.qd0[v], b.tau[:1, u], b.dt)):
+            assert rel(a.cpu().numpy(), r, 1e-12) < tol, (k, s.n)
+    row = tr.cpu().numpy()
+    assert np.array_equal(row[0, :oq[-1]], q1.cpu().numpy()) and np.array_equal(row[-1, oq[-1]:], qdT.cpu().numpy())
