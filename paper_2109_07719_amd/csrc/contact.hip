@@ -28,6 +28,7 @@
 // runs them.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 #include <type_traits>
@@ -154,8 +155,8 @@ struct GradArgs {
 };
 
 // The rollout gradient by the step's reverse statements, backwards in time:
-// per step, step_vjp recomputes the step from the stored state and runs the
-// adjoints of the integrator, the impulse update, both Gauss-Seidel solves
+// per step, step<true> recomputes the step from the stored state and step_vjp
+// runs the adjoints of the integrator, the impulse update, both Gauss-Seidel solves
 // (from their recorded sweeps), A and b, M^-1 J^T, the contact geometry and
 // the smooth step.  The next state and control are fetched a step ahead.
 template <typename S>
@@ -184,12 +185,77 @@ __global__ __launch_bounds__(kWave) void k_contact_adj(GradArgs<S> a) {
     const double u = un;
     if (t > 0) fetch(t - 1);
     wave::Step o;
-    const double ub = wave::step_vjp(a.tp, l, g, x, u, a.dt, a.tp.mu, xb, mub, o);
+    wave::step<true>(a.tp, l, g, x, u, a.dt, a.tp.mu, o);
+    const double ub = wave::step_vjp(a.tp, l, g, x, a.dt, a.tp.mu, xb, mub, o);
     if (live && l.one) a.gtau[((size_t)t * nu + l.ui) * B + s] = S(ub);
   }
   if (live) wave::store_state(xb, l, a.gq0, a.gqd0, B, s);
   mub = wave::rsum(mub);
   if (a.gmu && live && l.gl == 0) a.gmu[s] = S(mub);
+}
+
+// The same with two wavefronts per four systems, for batches that leave half
+// the SIMDs idle: they take the steps in turn, each with its own LDS, so that
+// one recomputes its step, which waits for nothing, while the other reverses
+// the step after it.  Nothing but the adjoint state goes from one to the
+// other.  A step costs its reverse alone, not both: 250 systems (63
+// workgroups), 30 sweeps, FP64: 87 -> 60 us a step.
+size_t pair_lds_bytes(const WTopo& tp) {
+  return 2 * wave_lds_bytes(tp) + (size_t)(wave::kStateNumbers + 1) * kWave * sizeof(double);
+}
+template <typename S>
+__global__ __launch_bounds__(2 * kWave) void k_contact_adj_pair(GradArgs<S> a) {
+  __shared__ int meta[kGrp];
+  wave::fill_meta(a.tp, meta);
+  __syncthreads();
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+  const int s0 = blockIdx.x * kSysWave + lane / kGrp;
+  const bool live = s0 < a.B;
+  const int s = live ? s0 : a.B - 1;
+  const size_t B = (size_t)a.B;
+  const wave::Lds g = wave::lds_of(a.tp, contact_lds, meta);  // by the group in the workgroup
+  double* const xch = contact_lds + 2 * (size_t)kSysWave * a.tp.stride + lane;
+  const wave::Lane l = wave::load_lane(a.tp, a.P, B, s);
+  const int nx = a.tp.nq + a.tp.nv, nu = a.tp.nu;
+  wave::State xb = wave::zero_state(), nxt = wave::zero_state(), x = wave::zero_state();
+  double un = 0, mub = 0;
+  auto fetch = [&](int t) {
+    if (t < 0) return;
+    const S* row = a.traj + (size_t)t * nx * B;
+    wave::load_state(nxt, l, row, row + (size_t)a.tp.nq * B, B, s);
+    if (l.one) un = double(a.tau[((size_t)t * nu + l.ui) * B + s]);
+  };
+  if (wid == 0) {
+    wave::load_state(xb, l, a.gqT, a.gqdT, B, s);
+    wave::each(xb, [&](int k, double& v) { xch[k * kWave] = v; });
+  }
+  fetch(a.T - 1 - wid);
+  wave::Step o;
+  for (int k = -1; k < a.T; ++k) {
+    const int t = a.T - 1 - k;  // the step to reverse
+    if (wid == (k & 1)) {
+      if (k >= 0) {
+        wave::each(xb, [&](int i, double& v) { v = xch[i * kWave]; });
+        const double ub = wave::step_vjp(a.tp, l, g, x, a.dt, a.tp.mu, xb, mub, o);
+        if (live && l.one) a.gtau[((size_t)t * nu + l.ui) * B + s] = S(ub);
+        wave::each(xb, [&](int i, double& v) { xch[i * kWave] = v; });
+      }
+    } else if (t > 0) {
+      x = nxt;
+      const double u = un;
+      fetch(t - 3);
+      wave::step<true>(a.tp, l, g, x, u, a.dt, a.tp.mu, o);
+    }
+    __syncthreads();
+  }
+  mub = wave::rsum(mub);
+  if (wid == 1) xch[wave::kStateNumbers * kWave] = mub;
+  __syncthreads();
+  if (wid == 0 && live) {
+    wave::each(xb, [&](int i, double& v) { v = xch[i * kWave]; });
+    wave::store_state(xb, l, a.gq0, a.gqd0, B, s);
+    if (a.gmu && l.gl == 0) a.gmu[s] = S(mub + xch[wave::kStateNumbers * kWave]);
+  }
 }
 
 int cfail(int code, const std::string& msg) { return aba::report_error(code, msg); }
@@ -220,8 +286,17 @@ CTopo constants_as_seen_by(CTopo tp) {
 
 template <typename S>
 hipError_t launch_grad(const GradArgs<S>& a, hipStream_t st) {
-  hipLaunchKernelGGL((k_contact_adj<S>), dim3((a.B + kSysWave - 1) / kSysWave), dim3(kWave), wave_lds_bytes(a.tp), st,
-                     a);
+  const int blocks = (a.B + kSysWave - 1) / kSysWave;
+  int dev = 0, cus = 0, lds = 0;
+  // two wavefronts while all of them are resident at once (one pair a CU for
+  // quadrupeds, by its LDS: FP32, one wavefront / two, 16 systems 85 / 60 us a
+  // step, 1000 systems 88 / 71, 2048 systems 92 / 141)
+  const bool pair = a.T > 1 && hipGetDevice(&dev) == hipSuccess &&
+                    hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+                    hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess &&
+                    (size_t)blocks <= cus * std::min<size_t>(2, lds / (pair_lds_bytes(a.tp) + kGrp * sizeof(int)));
+  if (pair) hipLaunchKernelGGL((k_contact_adj_pair<S>), dim3(blocks), dim3(2 * kWave), pair_lds_bytes(a.tp), st, a);
+  else hipLaunchKernelGGL((k_contact_adj<S>), dim3(blocks), dim3(kWave), wave_lds_bytes(a.tp), st, a);
   return hipGetLastError();
 }
 

@@ -307,6 +307,7 @@ __device__ __forceinline__ Lane load_lane(const WTopo& tp, const S* P, size_t B,
   return l;
 }
 
+constexpr int kStateNumbers = 15;
 // Per-lane state: a 1-dof link's q, qd; the root's pose and body velocity.
 struct State {
   D q, qd;
@@ -342,6 +343,14 @@ __device__ __forceinline__ void store_state(const State& x, const Lane& l, S* q,
 #pragma unroll
     for (int k = 0; k < 6; ++k) qd[(l.vi + k) * B + s] = S(b[k]);
   }
+}
+// the state's numbers in turn
+template <typename F>
+__device__ __forceinline__ void each(State& x, F&& f) {
+  D* const v[kStateNumbers] = {&x.q,      &x.qd,     &x.pos.x,  &x.pos.y,   &x.pos.z,   &x.quat.x,  &x.quat.y, &x.quat.z,
+                               &x.quat.w, &x.vel.a.x, &x.vel.a.y, &x.vel.a.z, &x.vel.l.x, &x.vel.l.y, &x.vel.l.z};
+#pragma unroll
+  for (int k = 0; k < kStateNumbers; ++k) f(k, *v[k]);
 }
 __device__ __forceinline__ State zero_state() {
   State x;
@@ -881,12 +890,12 @@ __device__ __forceinline__ void sweeps_rev(const Lane& l, const Step& o, D xb, D
   }
 }
 
-// The adjoint of the step at x: xb in, the adjoint of (q1, qd1), and out,
-// that of (q, qd); returns the control's adjoint, adds the friction
-// coefficient's share of this lane to mub.
-__device__ __forceinline__ D step_vjp(const WTopo& tp, const Lane& l, const Lds& g, const State& x, D u, D dt, D mu,
-                                      State& xb, D& mub, Step& o) {
-  step<true>(tp, l, g, x, u, dt, mu, o);
+// The adjoint of the step at x, from what step<true> left in o and in the
+// group's LDS (overwritten): xb in, the adjoint of (q1, qd1), and out, that of
+// (q, qd); returns the control's adjoint, adds the friction coefficient's
+// share of this lane to mub.
+__device__ __forceinline__ D step_vjp(const WTopo& tp, const Lane& l, const Lds& g, const State& x, D dt, D mu,
+                                      State& xb, D& mub, const Step& o) {
   const V3<D> z3 = aba::zero3<D>();
   const int dd = tp.dd;
   // ---- integrator
