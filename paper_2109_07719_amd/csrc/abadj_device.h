@@ -1693,16 +1693,18 @@ hipError_t launch_backward_frame(const BwdArgs<S>& a, const Tiling& tl, hipStrea
   // is pipelined while every batch is resident at once (or as chosen), with
   // two recomputing wavefronts if those fit too; K > 1 up to two rounds
   // (40 steps, us, one wave / NP = 1 / NP = 2; K = 1: quadrupeds, 256 batches
-  // 365 / 235 / 186, 512 381 / 258 / 368, 768 409 / 507 / 551; trees, 384 575
-  // / 355 / 409, 744 616 / 691 / 637; ball quadrupeds, 256 494 / 289, 512 514 /
-  // 575.  K = 10: quadrupeds, 256 576 / 296, 512 600 / 583, 768 621 / 873; ball
-  // quadrupeds, 512 730 / 665, 768 763 / 1002; trees, 384 844 / 688, 744 885 /
-  // 1089).  One step has nothing to overlap.
+  // 365 / 235 / 192, 512 381 / 258 / 368, 768 409 / 507 / 551; trees, 384 575
+  // / 355 / 409, 744 616 / 691 / 637; ball quadrupeds, 256 494 / 289 / 247, 512
+  // 514 / 575 / -.  K = 10: quadrupeds, 256 576 / 296 / 270, 512 600 / 583 / -,
+  // 768 621 / 873 / -; ball quadrupeds, 512 730 / 665 / -, 768 763 / 1002 / -;
+  // trees, 384 844 / 688 / -, 744 885 / 1089 / -).  One step has nothing to
+  // overlap.
   if (a.K == 1 && a.T > 1 && (!tl.chosen || tl.pipelined)) {
     if (launch_frame_pipe<S, F, E, 2, 0>(a, 1, st) || launch_frame_pipe<S, F, E, 1, 0>(a, tl.chosen ? 0 : 1, st))
       return hipGetLastError();
   }
-  if (a.K > 1 && a.T > 1 && launch_frame_pipe<S, F, E, 1, 1>(a, 2, st)) return hipGetLastError();
+  if (a.K > 1 && a.T > 1 && (launch_frame_pipe<S, F, E, 2, 1>(a, 2, st) || launch_frame_pipe<S, F, E, 1, 1>(a, 2, st)))
+    return hipGetLastError();
   return launch_backward_one<S, double, F, E, C, false, true>(a, tl, st);
 }
 

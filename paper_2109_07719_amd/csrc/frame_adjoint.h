@@ -165,10 +165,14 @@ __device__ __forceinline__ V6<double> from_point(const V3<double>& n, const V3<d
   return v6<double>(n + cross(o, f), f);
 }
 
-// acc: the 1-dof joint's acceleration
-template <bool FREE, bool BALL, typename S>
+// acc: the 1-dof joint's acceleration.  half: called half way, by every lane
+struct Nothing {
+  __device__ void operator()() const {}
+};
+template <bool FREE, bool BALL, typename S, typename H = Nothing>
 __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, const State<double, FREE>& st,
-                                                     const V3<double>& ctl, double* xb, double* acc = nullptr) {
+                                                     const V3<double>& ctl, double* xb, double* acc = nullptr,
+                                                     H&& half = H()) {
   FrameStep o;
   const V3<double> z3 = zero3<double>();
   o.q = st.q[0];
@@ -276,6 +280,7 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
   body.Ib = o.I;
   V6<double> F = inertia_mul(body, A0) + crf(o.V, inertia_mul(body, o.V));
   SySp<double> IA = inertia_sysp(body);
+  half();
   // ---- articulated inertias and bias forces, leaves to root
   double u = 0;
   V3<double> ub = z3, yb = z3;
@@ -603,31 +608,31 @@ struct FramePipe {
   // numbers of a replayed state in the ring (slots, then mfree extended ones)
   static __host__ __device__ int state(int mfree) { return 2 * kWave + 11 * mfree; }
   static __host__ __device__ size_t lds(int K, int mfree) {
-    return (size_t)(2 * NP * TW + (NP + 1) * rec) * sizeof(double) +
-           NR * ((size_t)3 * K * state(mfree) + rec) * sizeof(S);
+    return (size_t)(2 * TW + (NP + 1) * rec) * sizeof(double) + NR * ((size_t)3 * K * state(mfree) + rec) * sizeof(S);
   }
 };
 
-// Pipelined backward rollout, K >= 1, in phases of NP steps ended by a
-// workgroup barrier.  The recomputes do not depend on one another: in phase k
-// producer j recomputes the phase's step j into buffer k % 2 while the consumer
-// reverses the steps of phase k - 1.  K > 1 (NR = 1): one more wavefront
-// replays the segment before, a share of its steps each phase, into a ring of
-// three segments of states in LDS (one replayed, one recomputed, the last
-// steps of one still to be reversed), so that a segment costs its slowest
+// Pipelined backward rollout, K >= 1, in time slots ended by a workgroup
+// barrier, one reversed step a slot.  The recomputes do not depend on one
+// another: with NP producers a step's recompute takes NP slots (with two, a
+// barrier after the velocities and inertias, which is about half of it), the last of them the one before its reverse, and only that
+// one writes the step's record, so that two records are enough.  K > 1 (NR =
+// 1): one more wavefront replays the segment before, a step a slot, into a
+// ring of three segments of states in LDS (one replayed, one recomputed, the
+// last steps of one still to be reversed), so that a segment costs its slowest
 // part and not replay, recompute and reverse in turn.  The reversing wavefront
-// bounds K == 1 with two recomputing ones (4.6 us a step of a quadruped), the
-// recomputing one K > 1 (6 us).  Adjoints of 1024 quadrupeds x 200 steps in
-// segments of 10, 2.86 -> 1.24 ms; of 1024 ball-jointed ones x 100 steps, K =
-// 1, 1.22 -> 0.70 ms.
+// bounds K == 1, the replaying one K > 1.  Adjoints, one wavefront / one
+// producer / two: 1024 quadrupeds x 200 steps in segments of 10, 2.86 / 1.24 /
+// 1.16 ms; 1024 ball-jointed ones x 100 steps, K = 1, 1.22 / 0.70 / 0.60.
 template <typename S, bool FREE, int FR, int NP, int NR>
 __global__ __launch_bounds__((NP + NR + 1) * kWave)
 __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(BwdArgs<S> A) {
   using P = FramePipe<S, FREE, FR, NP, NR>;
   constexpr bool BALL = P::BALL;
-  const int wid = threadIdx.x / kWave;
+  static_assert(NP == 1 || NP == 2, "one barrier half way");
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   double* const tape = lds<double>();
-  double* const xbs = tape + 2 * NP * P::TW;
+  double* const xbs = tape + 2 * P::TW;
   S* const xreplay = reinterpret_cast<S*>(xbs + (NP + 1) * P::rec);
   S* const ring = xreplay + P::rec;
   const int wb = blockIdx.x;
@@ -636,41 +641,46 @@ __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(Bw
   const int ns = A.P.nslots, nu = A.P.nu, nf = A.P.nfree, mf = A.P.mfree, T = A.T;
   const size_t RW = state_record(ns, nf);
   const bool act = l.active();
-  // K > 1: segments last to first, each ppseg phases; replay runs ppseg
-  // phases ahead.  K == 1: one segment of T steps
-  const int seg = NR ? A.K : T, nseg = (T + seg - 1) / seg;
-  const int ppseg = (seg + NP - 1) / NP, ahead = NR ? ppseg : 0, phases = ahead + nseg * ppseg;
+  // K > 1: segments last to first, and in each its steps; the first one may be
+  // short of seg.  K == 1: one segment of T steps
+  const int seg = NR ? A.K : T, nseg = (T + seg - 1) / seg, steps = nseg * seg;
+  const int ahead = (NR ? seg : 0) + NP, slots = steps + ahead;  // step n is reversed in slot n + ahead
   const unsigned long long extended = __ballot(l.fidx >= 0);
   const int rl = l.fidx < 0 ? -1 : __popcll(extended & ((1ull << l.lane) - 1));
   const int sw = P::state(mf);
   auto length = [&](int c) { return min(seg, T - (nseg - 1 - c) * seg); };  // of the c-th segment
-  auto time_of = [&](int c, int i) { return (nseg - 1 - c) * seg + length(c) - 1 - i; };
-  // step i (counted from its end) of the c-th segment
-  auto get = [&](int c, int i, State<S, FREE>& st) {
+  auto has = [&](int n) { return n < steps && n % seg < length(n / seg); };
+  auto time_of = [&](int n) { return (nseg - 1 - n / seg) * seg + length(n / seg) - 1 - n % seg; };
+  auto get = [&](int n, State<S, FREE>& st) {
     if (!act) return;
-    if constexpr (NR > 0) get_slot(st, ring + (size_t)((c % 3) * seg + length(c) - 1 - i) * sw, kWave, mf, l.lane, rl);
-    else get_slot(st, A.ck + (size_t)time_of(c, i) * RW, ns, nf, l.slot, l.fidx);
+    const int c = n / seg;
+    if constexpr (NR > 0) get_slot(st, ring + (size_t)((c % 3) * seg + length(c) - 1 - n % seg) * sw, kWave, mf, l.lane, rl);
+    else get_slot(st, A.ck + (size_t)time_of(n) * RW, ns, nf, l.slot, l.fidx);
   };
-  constexpr bool CTL3 = BALL;
+  int slot = 0;
+  auto next_slot = [&] {
+    __syncthreads();
+    ++slot;
+  };
   if (NR > 0 && wid < NR) {
     const auto SC = step_const<false, kFrameStep<false, S>, FR>(A.P, l, load_linkc<S, FR>(A.P, l), maxd);
     State<S, FREE> st = {};
-    for (int k = 0; k <= phases; ++k) {
-      const int c = k / ppseg, part = k % ppseg;
+    while (slot < slots) {
+      const int c = slot / seg, i = slot % seg;
       if (c < nseg) {
-        const int n = length(c), share = (seg - 1 + ppseg - 1) / ppseg, t0 = (nseg - 1 - c) * seg;
+        const int t0 = (nseg - 1 - c) * seg;
         S* const base = ring + (size_t)(c % 3) * seg * sw;
-        if (part == 0 && act) {
+        if (i == 0 && act) {
           get_slot(st, A.ck + (size_t)(nseg - 1 - c) * RW, ns, nf, l.slot, l.fidx);
           put_slot(st, base, kWave, mf, l.lane, rl);
         }
-        for (int j = part * share + 1; j <= min((part + 1) * share, n - 1); ++j) {
-          const V3<S> tau = act ? load_ctl<CTL3>(A.tau + (size_t)(t0 + j - 1) * nu, l) : zero3<S>();
+        if (i + 1 < length(c)) {
+          const V3<S> tau = act ? load_ctl<BALL>(A.tau + (size_t)(t0 + i) * nu, l) : zero3<S>();
           advance<FR, false, false>(A.P, gravity(A.P), l, SC, st, tau, A.dt, maxd, xreplay);
-          if (act) put_slot(st, base + (size_t)j * sw, kWave, mf, l.lane, rl);
+          if (act) put_slot(st, base + (size_t)(i + 1) * sw, kWave, mf, l.lane, rl);
         }
       }
-      __syncthreads();
+      next_slot();
     }
   } else if (wid < NR + NP) {
     const int j = wid - NR;
@@ -678,28 +688,29 @@ __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(Bw
     const FrameLane<S> p = frame_lane<S, FR>(A.P, l, maxd);
     State<S, FREE> nxt = {};
     V3<S> nt = zero3<S>();
-    auto fetch = [&](int k) {  // phase k's step, if it has one
-      const int c = (k - ahead) / ppseg, i = (k - ahead) % ppseg * NP + j;
-      if (k < ahead || c >= nseg || i >= length(c)) return;
-      if constexpr (NR == 0) get(c, i, nxt);
-      if (act) nt = load_ctl<CTL3>(A.tau + (size_t)time_of(c, i) * nu, l);
+    auto fetch = [&](int n) {
+      if (!has(n)) return;
+      if constexpr (NR == 0) get(n, nxt);
+      if (act) nt = load_ctl<BALL>(A.tau + (size_t)time_of(n) * nu, l);
     };
-    fetch(ahead);
-    for (int k = 0; k <= phases; ++k) {
-      const int c = (k - ahead) / ppseg, i = (k - ahead) % ppseg * NP + j;
-      if (k >= ahead && c < nseg && i < length(c)) {
-        if constexpr (NR > 0) get(c, i, nxt);
+    fetch(j);
+    for (int n = j; n < steps; n += NP) {
+      while (slot < n + ahead - NP) next_slot();
+      if (has(n)) {
+        if constexpr (NR > 0) get(n, nxt);
         const State<double, FREE> st = cvt_state<double>(nxt);
         const V3<double> tau = cvt3<double>(nt);
-        fetch(k + 1);
-        FrameStep o = frame_recompute<FREE, BALL>(p, st, limit_tau<FR>(A.P, l, st, tau), xb);
-        double* const tp = tape + ((k & 1) * NP + j) * P::TW;
+        fetch(n + NP);
+        FrameStep o = frame_recompute<FREE, BALL>(p, st, limit_tau<FR>(A.P, l, st, tau), xb, nullptr, [&] {
+          if constexpr (NP == 2) next_slot();
+        });
+        double* const tp = tape + (n & 1) * P::TW;
         frame_fields<FREE, BALL>(o, [&](int f, double& v) { tp[f * kWave + l.lane] = v; });
-      } else if (k >= ahead) {
-        fetch(k + 1);
+      } else {
+        fetch(n + NP);
       }
-      __syncthreads();
     }
+    while (slot < slots) next_slot();
   } else {
     double* const xb = xbs + NP * P::rec;
     const FrameLane<S> p = frame_lane<S, FR>(A.P, l, maxd);
@@ -707,19 +718,18 @@ __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(Bw
     int nonfin = 0;
     State<double, FREE> x1 = seed_state<S, double, FREE>(A, l);
     State<S, FREE> nxt = {};
-    if constexpr (FREE && NR == 0) get(0, 0, nxt);
-    for (int k = 0; k <= phases; ++k) {
-      const int c = k > ahead ? (k - 1 - ahead) / ppseg : nseg, i0 = (k - 1 - ahead) % ppseg * NP;
-      for (int j = 0; j < NP && c < nseg && i0 + j < length(c); ++j) {
-        const int i = i0 + j;
+    if constexpr (FREE && NR == 0) get(0, nxt);
+    while (slot < ahead) next_slot();
+    for (int n = 0; n < steps; ++n) {
+      if (has(n)) {
         FrameStep o;
-        const double* tp = tape + (((k - 1) & 1) * NP + j) * P::TW;
+        const double* tp = tape + (n & 1) * P::TW;
         frame_fields<FREE, BALL>(o, [&](int f, double& v) { v = tp[f * kWave + l.lane]; });
         State<double, FREE> st = {};
         if constexpr (FREE) {
-          if constexpr (NR > 0) get(c, i, nxt);
+          if constexpr (NR > 0) get(n, nxt);
           st = cvt_state<double>(nxt);
-          if (NR == 0 && i + 1 < T) get(0, i + 1, nxt);
+          if (NR == 0 && has(n + 1)) get(n + 1, nxt);
         } else {
           st.q[0] = o.q;
           st.qd[0] = o.qd;
@@ -727,9 +737,9 @@ __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(Bw
         double lq, lqd;
         limit_slopes<FR>(A.P, l, st, lq, lqd);
         const V3<double> taub = frame_reverse<FREE, BALL>(p, o, st, dt, lq, lqd, x1, xb);
-        frame_outputs<S, FREE>(A, l, time_of(c, i), taub, x1, nonfin);
+        frame_outputs<S, FREE>(A, l, time_of(n), taub, x1, nonfin);
       }
-      __syncthreads();
+      next_slot();
     }
     if (act) {
       const State<S, FREE> x0 = cvt_state<S>(x1);
