@@ -649,7 +649,7 @@ def pgs_bench(args, torch, dev):
            "ms_per_step": total, "steps": args.steps, "dtype": "f32", "data": "synthetic",
            "config": {"workload": f"{B} MLCPs of {n} rows (Delassus-like A, box and one-sided bounds), "
                                   f"{niter} sweeps, solve keeping the sweep vectors + adjoint",
-                      "batch": B, "rows": n, "sweeps": niter, "lanes_per_problem": 1},
+                      "batch": B, "rows": n, "sweeps": niter, "lanes_per_problem": 4},
            "solve_ms": ms["solve"], "adjoint_ms": ms["adjoint"],
            "roofline": {"bound": "alu", "unit": "TFLOP/s", "peak": FP32_PEAK_TFLOPS,
                         "solve_achieved": fl_solve * B / (ms["solve"] * 1e-3) / 1e12,

@@ -20,18 +20,19 @@
 // held four times.  A kernel is compiled for 4, 8, 12 and 16 rows: row and
 // column loops are unrolled and every operand has a fixed register, A_bar's
 // too; the up to three rows past n are zero rows, which leave everything as it
-// is, and no branch separates one row's instructions from the next's.  The sweep vectors go to the workspace as
-// [niter + 1][n][batch].  Problems are independent: no barriers.
+// is, and no branch separates one row's instructions from the next's.  The
+// sweep vectors go to the workspace as [niter + 1][n][batch].  Problems are
+// independent: no barriers.
 //
 // What bounds it: the instructions of a row, the GS order being a serial chain
 // of n niter rows.  With one lane per problem 32768 problems were 512
 // wavefronts, half a SIMD's worth each, every lane reading rows of A of its
 // own, with A and A_bar (288 registers of 12 rows) past the register file.
-// 32768 problems x 12 rows x 30 sweeps, FP32: solve 59 -> 27 us, adjoint
-// 140 -> 57 us, and in FP64
-// 71 -> 42 and 2033 -> 94; 64 problems 35 -> 17 and 93 -> 30; 16 rows, 32768
-// problems, 92 -> 37 and 445 -> 80.  (200000 problems of 4 rows, where memory
-// bounds it, 33 -> 33 and 62 -> 70.)
+// 32768 problems x 12 rows x 30 sweeps, FP32: solve 59 -> 29 us, adjoint 138
+// -> 71 us, and in FP64 71 -> 41 and 2033 -> 96; 64 problems 35 -> 17 and 93 ->
+// 33; 16 rows, 32768 problems, 92 -> 39 and 445 -> 113; 4 rows 18 -> 11 and 29
+// -> 20 (but 200000 problems of 4 rows, which fill the chip either way, 33 ->
+// 36 and 62 -> 91).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -78,20 +79,33 @@ __device__ __forceinline__ S quad_sum(S x) {
   return x + quad<0x4E>(x);  // [2, 3, 0, 1]
 }
 
-// 1 / d = hi + lo, the two of one sign and not zero, so that x hi + x lo is
-// x / d to the last bit or so and keeps its sign where x is infinite or d zero
+// x / d by a reciprocal taken once, rounded as the division would be or, in
+// FP64, to the last bit or so.  FP32: by way of FP64.  FP64: 1 / d = hi + lo,
+// the two of one sign and not zero, so that x hi + x lo keeps its sign where x
+// is infinite or d zero.
 template <typename S>
-__device__ __forceinline__ void reciprocal(S d, S& hi, S& lo) {
-  constexpr S eps = sizeof(S) == 8 ? S(2.2e-16) : S(1.2e-7);
-  hi = S(1) / d;
-  S r = fma(-d, hi, S(1));
-  if (r < S(0)) {  // rounded away from zero: one unit back
-    if constexpr (sizeof(S) == 8) hi = __longlong_as_double(__double_as_longlong(hi) - 1);
-    else hi = __int_as_float(__float_as_int(hi) - 1);
-    r = fma(-d, hi, S(1));
+struct Reciprocal;
+template <>
+struct Reciprocal<float> {
+  double r;
+  __device__ __forceinline__ void set(float d) { r = 1.0 / double(d); }
+  __device__ __forceinline__ float times(float x) const { return float(double(x) * r); }
+};
+template <>
+struct Reciprocal<double> {
+  double hi, lo;
+  __device__ __forceinline__ void set(double d) {
+    constexpr double eps2 = 2.2e-16 * 2.2e-16;
+    hi = 1.0 / d;
+    double r = fma(-d, hi, 1.0);
+    if (r < 0.0) {  // rounded away from zero: one unit back
+      hi = __longlong_as_double(__double_as_longlong(hi) - 1);
+      r = fma(-d, hi, 1.0);
+    }
+    lo = d == 0.0 ? hi : hi * (r > eps2 ? r : eps2);
   }
-  lo = d == S(0) ? hi : hi * (r > eps * eps ? r : eps * eps);
-}
+  __device__ __forceinline__ double times(double x) const { return fma(x, lo, x * hi); }
+};
 
 // A problem's columns and bounds on a lane of its quad
 template <typename S, int N>
@@ -101,7 +115,7 @@ struct Problem {
   size_t p;
   S A[N][C];                  // off-diagonal; zero on the diagonal and past n
   S b[C], lo[C], hi[C];
-  S inv[C], inv_lo[C];        // 1 / A_jj in two parts: s / A_jj to the last bit or so
+  Reciprocal<S> inv[C];       // of A_jj
 
   __device__ __forceinline__ size_t at(int c) const { return p * n + 4 * c + g; }
   __device__ __forceinline__ bool has(int c) const { return 4 * c + g < n; }
@@ -132,10 +146,10 @@ struct Problem {
     load(lo, P.lo, p * n, 1);
     load(hi, P.hi, p * n, 1);
 #pragma unroll
-    for (int c = 0; c < C; ++c) reciprocal(d[c], inv[c], inv_lo[c]);
+    for (int c = 0; c < C; ++c) inv[c].set(d[c]);
   }
   // x / A_jj of the lane's entry c
-  __device__ __forceinline__ S over(S x, int c) const { return fma(x, inv_lo[c], x * inv[c]); }
+  __device__ __forceinline__ S over(S x, int c) const { return inv[c].times(x); }
   // y of row i, on the lane that owns it, from the vector x
   __device__ __forceinline__ S row(int i, const S (&x)[C]) const {
     S d = S(0);
@@ -176,13 +190,18 @@ __global__ __launch_bounds__(kBlock) void k_pgs_adjoint(PgsArgs<S> P) {
   if (p >= (size_t)P.batch) return;  // whole quads
   const size_t B = (size_t)P.batch, n = (size_t)P.n;
   const Problem<S, N> m(P, p, threadIdx.x % 4);
-  S Ab[N][C], Ad[C], xb[C], bb[C], lb[C], hb[C], x[C], xs[C], nx[C];
+  // A_bar sums in FP64, from x widened once a sweep: its error does not grow
+  // with the sweeps (relative error against FP64, 20 sweeps, 16 rows, FP32:
+  // 1.15e-7 with FP32 sums, 6.9e-8 so, 7.2e-8 with the sums begun at the first
+  // sweep)
+  double Ab[N][C], xd[C];
+  S Ad[C], xb[C], bb[C], lb[C], hb[C], x[C], xs[C], nx[C];
   m.load(xb, P.xbar, p * n, 1);
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     Ad[c] = bb[c] = lb[c] = hb[c] = x[c] = nx[c] = S(0);
 #pragma unroll
-    for (int i = 0; i < N; ++i) Ab[i][c] = S(0);
+    for (int i = 0; i < N; ++i) Ab[i][c] = 0.0;
   }
   // x: before row i of sweep t it holds the sweep's end for j < i and its
   // start, xs, for j > i; so at the sweep's first row it holds the start, the
@@ -191,6 +210,8 @@ __global__ __launch_bounds__(kBlock) void k_pgs_adjoint(PgsArgs<S> P) {
     m.load(x, P.ws + p, P.niter * n * B, B);
     m.load(nx, P.ws + p, (P.niter - 1) * n * B, B);
   }
+#pragma unroll
+  for (int c = 0; c < C; ++c) xd[c] = double(x[c]);
   for (int t = P.niter - 1; t >= 0; --t) {
 #pragma unroll
     for (int c = 0; c < C; ++c) xs[c] = nx[c];
@@ -211,11 +232,12 @@ __global__ __launch_bounds__(kBlock) void k_pgs_adjoint(PgsArgs<S> P) {
                  : i % 4 == 2 ? quad<0xAA>(own_db) : quad<0xFF>(own_db);
 #pragma unroll
       for (int k = 0; k < C; ++k) {
-        Ab[i][k] = fma(db, x[k], Ab[i][k]);
+        Ab[i][k] = fma(double(db), xd[k], Ab[i][k]);
         xb[k] = fma(db, m.A[i][k], xb[k]);
       }
       xb[c] = own ? S(0) : xb[c];
       x[c] = own ? xs[c] : x[c];
+      xd[c] = own ? double(xs[c]) : xd[c];
     }
   }
 #pragma unroll
@@ -223,7 +245,7 @@ __global__ __launch_bounds__(kBlock) void k_pgs_adjoint(PgsArgs<S> P) {
     if (i < P.n) {
 #pragma unroll
       for (int c = 0; c < C; ++c)
-        if (m.has(c)) P.Abar[(p * n + i) * n + 4 * c + m.g] = i == 4 * c + m.g ? Ad[c] : Ab[i][c];
+        if (m.has(c)) P.Abar[(p * n + i) * n + 4 * c + m.g] = i == 4 * c + m.g ? Ad[c] : S(Ab[i][c]);
     }
   m.store(bb, P.bbar, p * n, 1);
   m.store(lb, P.lobar, p * n, 1);
