@@ -215,7 +215,9 @@ int sim_status(sim_t h, void *stream, int *nonfinite_count);
  * A choice whose LDS would exceed the device's per-workgroup limit is
  * reduced at launch.  Default (from occupancy): 4 waves per block;
  * pipelined with 2 pairs per block while the pipelined pairs fit one
- * wavefront per SIMD, otherwise not pipelined.  Not thread-safe against
+ * wavefront per SIMD, otherwise not pipelined.  Until a tiling is set or
+ * tuned, kernels with rules of their own go by those (one wavefront per
+ * block; the FP64 adjoints by the number of batches).  Not thread-safe against
  * concurrent launches on the same handle.  Errors: SIM_ERR_INVALID_ARG. */
 typedef struct {
   int32_t waves_per_block;
