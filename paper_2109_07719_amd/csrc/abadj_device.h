@@ -832,21 +832,11 @@ __device__ __forceinline__ void integrate_lane(State<S, FREE>& st, const Lane& l
 template <int FR, bool CHAIN, typename R>
 constexpr bool kPlanarStep = CHAIN && FR == kFrIdentity && sizeof(R) == sizeof(double);
 
-// Whether they take the base-frame step (frame_adjoint.h): FP64 handles, but
-// for the chain kernels; store-all (MODE 2) keeps the general step's tape.
-// 40 steps in FP64, general / base frame: 1024 quadrupeds 310 / 203 us, 1024
-// ball-jointed ones 356 / 252, 300 trees 509 / 284, 8000 trees 1062 / 706.  An
-// FP32 handle keeps the general step, whose rounding errors do not grow with a
-// link's distance from the base (and at 8000 trees it is the faster, 423).
-template <bool CHAIN, typename T, int MODE = 1>
-constexpr bool kFrameStep = !CHAIN && std::is_same_v<T, double> && MODE != 2;
-
 // The constants a forward step reads, loaded once (inside the time loop a
 // store could alias them, and every step would wait for them).
-template <bool PLANAR, bool FRAME, int FR, typename T, typename S>
-__device__ __forceinline__ auto step_const(const Packed<S>& P, const Lane& l, const LinkC<T>& L, int maxd) {
+template <bool PLANAR, typename T, typename S>
+__device__ __forceinline__ auto step_const(const Packed<S>& P, const Lane& l, const LinkC<T>& L) {
   if constexpr (PLANAR) return planar_const<T>(P, l);
-  else if constexpr (FRAME) return frame_lane<S, FR>(P, l, maxd);
   else return L;
 }
 // One forward step of the lane's state under the control tau, as every
@@ -858,11 +848,6 @@ __device__ __forceinline__ void advance(const Packed<S>& P, const V3<T>& g, cons
   if constexpr (PLANAR) {
     const T qdd = planar_qdd<T>(g, L, st.q[0], st.qd[0], tau.x, maxd);
     if (l.active()) integrate_joint(st.q[0], st.qd[0], qdd, dt);
-  } else if constexpr (!std::is_same_v<LC, LinkC<T>>) {
-    Step<T> o;
-    const auto f = frame_recompute<FREE, BALL>(L, st, limit_tau<FR>(P, l, st, tau), xb, &o.t.qdd);
-    o.abase = f.abase;
-    if (l.active()) integrate_lane<T, FREE, BALL>(st, l, o, dt);
   } else {
     Step<T> o;
     aba_wave<T, FREE, CHAIN, BALL>(g, l, L, st, limit_tau<FR>(P, l, st, tau), maxd, xb, o);
@@ -932,7 +917,7 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_forward(FwdArgs<S
   const int nu = A.P.nu;
   constexpr bool BALL = FREE && FR == kFrBall;
   const LinkC<S> L = load_linkc<S, FR>(A.P, l);
-  const auto SC = step_const<PLANAR, kFrameStep<CHAIN, S, MODE>, FR>(A.P, l, L, maxd);
+  const auto SC = step_const<PLANAR>(A.P, l, L);
   State<S, FREE> st = {};
   if (l.active()) load_state(st, l, A.q0, A.qd0);
   V3<S> tau_next = (l.active() && A.T > 0) ? load_ctl<BALL>(A.tau, l) : zero3<S>();
@@ -1291,7 +1276,7 @@ __attribute__((amdgpu_waves_per_eu(FRAME ? (FREE ? 1 : 2) : (FREE || sizeof(R) >
   const LinkC<S> L = load_linkc<S, FR>(A.P, l);
   const LinkC<R> LR = widen<R>(L);
   constexpr bool PLANAR = kPlanarStep<FR, CHAIN, R>;
-  const auto SC = step_const<PLANAR, kFrameStep<CHAIN, S>, FR>(A.P, l, L, maxd);
+  const auto SC = step_const<PLANAR>(A.P, l, L);
   int nonfin = 0;  // non-finite outputs
   ParamBar<R> pg;
   param_bar_zero(pg);
@@ -1529,7 +1514,7 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_forward_jvp(JvpAr
   const int maxd = wave_maxd(A.P, wb);
   const int nu = A.P.nu;
   constexpr bool PLANAR = CHAIN && FR == kFrIdentity;
-  const auto SC = step_const<PLANAR, false, FR>(A.P, l, dual_const(load_linkc<S, FR>(A.P, l)), maxd);
+  const auto SC = step_const<PLANAR>(A.P, l, dual_const(load_linkc<S, FR>(A.P, l)));
   const V3<D> g = v3<D>(D(A.P.g[0], S(0)), D(A.P.g[1], S(0)), D(A.P.g[2], S(0)));
   const D dt = D(A.dt, S(0));
   State<S, FREE> sv = {}, sd = {};

@@ -1,5 +1,4 @@
-// The FP64 adjoint (and an FP64 handle's forward step: frame_recompute alone)
-// of trees, free roots, prismatic and ball joints and joint
+// The FP64 adjoint of trees, free roots, prismatic and ball joints and joint
 // limits, in the base frame, by the adjoint of the inverse dynamics: with w =
 // M^-1 (dt qd1_bar) (two sweeps with the step's articulated factors),
 //   tau_bar = w,  (q_bar, qd_bar) -= d/d(q, qd) <w, ID(q, qd, qdd)> at fixed qdd
@@ -165,14 +164,13 @@ __device__ __forceinline__ V6<double> from_point(const V3<double>& n, const V3<d
   return v6<double>(n + cross(o, f), f);
 }
 
-// acc: the 1-dof joint's acceleration.  half: called half way, by every lane
+// half: called half way, by every lane
 struct Nothing {
   __device__ void operator()() const {}
 };
 template <bool FREE, bool BALL, typename S, typename H = Nothing>
 __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, const State<double, FREE>& st,
-                                                     const V3<double>& ctl, double* xb, double* acc = nullptr,
-                                                     H&& half = H()) {
+                                                     const V3<double>& ctl, double* xb, H&& half = H()) {
   FrameStep o;
   const V3<double> z3 = zero3<double>();
   o.q = st.q[0];
@@ -360,7 +358,6 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
   }
   o.F = mul(IA, a) + F;
   o.Ap = ap + A0 - cb;
-  if (acc != nullptr) *acc = qdd;
   if constexpr (FREE) {
     if (p.root) root_pack(o, f);
   }
@@ -663,7 +660,7 @@ __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(Bw
     ++slot;
   };
   if (NR > 0 && wid < NR) {
-    const auto SC = step_const<false, kFrameStep<false, S>, FR>(A.P, l, load_linkc<S, FR>(A.P, l), maxd);
+    const LinkC<S> L = load_linkc<S, FR>(A.P, l);
     State<S, FREE> st = {};
     while (slot < slots) {
       const int c = slot / seg, i = slot % seg;
@@ -676,7 +673,7 @@ __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(Bw
         }
         if (i + 1 < length(c)) {
           const V3<S> tau = act ? load_ctl<BALL>(A.tau + (size_t)(t0 + i) * nu, l) : zero3<S>();
-          advance<FR, false, false>(A.P, gravity(A.P), l, SC, st, tau, A.dt, maxd, xreplay);
+          advance<FR, false, false>(A.P, gravity(A.P), l, L, st, tau, A.dt, maxd, xreplay);
           if (act) put_slot(st, base + (size_t)(i + 1) * sw, kWave, mf, l.lane, rl);
         }
       }
@@ -701,7 +698,7 @@ __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(Bw
         const State<double, FREE> st = cvt_state<double>(nxt);
         const V3<double> tau = cvt3<double>(nt);
         fetch(n + NP);
-        FrameStep o = frame_recompute<FREE, BALL>(p, st, limit_tau<FR>(A.P, l, st, tau), xb, nullptr, [&] {
+        FrameStep o = frame_recompute<FREE, BALL>(p, st, limit_tau<FR>(A.P, l, st, tau), xb, [&] {
           if constexpr (NP == 2) next_slot();
         });
         double* const tp = tape + (n & 1) * P::TW;
