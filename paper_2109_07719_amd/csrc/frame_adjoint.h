@@ -7,13 +7,23 @@
 //
 // What bounds these kernels is the instructions a wavefront issues over the
 // levels of a tree, where one lane in six works.  So every spatial quantity is
-// taken about one origin in one frame (a fixed base's; a free root's own,
-// where its motion subspace is the identity): the level loops then add and
-// transform nothing, poses and velocities come from ancestor-doubling rounds
-// (log2 of the depth) instead of levels, and what the reverse needs beyond
-// the two sweeps is one sum over each subtree.  Adjoints of 8192 trees x 50
-// steps 2.83 -> 1.60 ms, of 1024 quadrupeds x 200 steps in segments of 10
-// (replay included) 4.74 -> 2.86 ms.
+// in the axes of one frame (a fixed base's; a free root's own, where its motion
+// subspace is the identity): the level loops rotate nothing, poses and
+// velocities come from ancestor-doubling rounds (log2 of the depth) instead of
+// levels, and what the reverse needs beyond the two sweeps is one sum over each
+// subtree.  Adjoints of 8192 trees x 50 steps 2.83 -> 1.60 ms, of 1024
+// quadrupeds x 200 steps in segments of 10 (replay included) 4.74 -> 2.86 ms.
+//
+// Where they are taken about is a matter of the handle's type (kOwnOrigin).  An
+// FP32 handle's: about the root's joint origin, and nothing is shifted either.
+// An inertia there holds the squared distance from it, and a joint's small
+// numbers are what is left of that; FP32 outputs do not show it.  An FP64
+// handle's: each link's about its own joint's origin, shifted by d, the step
+// from the parent's origin to the link's, where they pass from link to link.
+// Error of tau_bar, one step of a 20-link tree in FP64, link frames / one
+// origin / own origins: at the base 2.2e-16 / 3.9e-15 / 2.9e-15, mounted 10 m
+// off it 2.2e-16 / 2.2e-13 / 2.9e-15.  8192 trees x 50 steps in an FP32 handle with own
+// origins: 1.60 -> 1.90 ms.
 //
 // A ball joint's three axes turn with its link; its subspace is every
 // rotation about the joint's origin o, S = [1; [o]x], and its block form is
@@ -27,6 +37,9 @@ namespace aba {
 namespace {
 
 constexpr int kJumps = 6;  // doubling rounds for up to 64 levels
+
+template <typename S>
+constexpr bool kOwnOrigin = sizeof(S) == sizeof(double);
 
 // The link's constants stay in the handle's type S (FP32 ones widen exactly
 // where they are used, at a third of the registers' cost).
@@ -72,30 +85,62 @@ __device__ __forceinline__ FrameLane<S> frame_lane(const Packed<S>& P, const Lan
   return p;
 }
 
-// v summed over the link and its ancestors, by doubling rounds through the
-// exchange records (a round: one write and one read of every lane).
+// From one origin to another, d the step from the parent's to the link's: a
+// motion goes down it, a force and an inertia up.
+__device__ __forceinline__ V6<double> down(const V3<double>& d, const V6<double>& v) {
+  return v6<double>(v.a, v.l + cross(v.a, d));
+}
+__device__ __forceinline__ V6<double> up(const V3<double>& d, const V6<double>& f) {
+  return v6<double>(f.a + cross(d, f.l), f.l);
+}
+__device__ __forceinline__ SySp<double> up(const V3<double>& d, const SySp<double>& M) {
+  M3<double> E;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) E.m[k] = k % 4 == 0 ? 1.0 : 0.0;
+  return congruence_XT(E, d, M);
+}
+
+// Motions v of the link and its ancestors summed, about the link's origin: by
+// doubling rounds through the exchange records (a round: one write and one
+// read of every lane).  With own origins a round also carries the step D over
+// the links summed so far.
 template <typename S>
-__device__ __forceinline__ V6<double> path_sum(const FrameLane<S>& p, V6<double> v, double* xb) {
+__device__ __forceinline__ V6<double> path_sum(const FrameLane<S>& p, V6<double> v, V3<double> D, double* xb) {
 #pragma unroll
   for (int r = 0; r < kJumps; ++r) {
     if (1 << r > p.maxd) break;
     put6(xb, 0, p.lane, v);
+    if constexpr (kOwnOrigin<S>) {
+      const double t[4] = {D.x, D.y, D.z, 0.0};
+      put_rec(xb, p.lane, 6, t);
+    }
     wave_sync();
-    if (p.anc[r] >= 0) v = get6(xb, 0, p.anc[r]) + v;
+    if (p.anc[r] >= 0) {
+      V6<double> u = get6(xb, 0, p.anc[r]);
+      if constexpr (kOwnOrigin<S>) {
+        double t[4];
+        get_rec(xb, p.anc[r], 6, t);
+        u = down(D, u);
+        D = v3<double>(t[0], t[1], t[2]) + D;
+      }
+      v = u + v;
+    }
     wave_sync();
   }
   return v;
 }
 
 // A step's quantities that its reverse reads.  A free root keeps its 6 x 6
-// factor M = L^T D L in S, U, Di, Ap, F (root_pack), which it does not use.
+// factor M = L^T D L in ax, U, Di, Ap, F (root_pack), which it does not use.
 struct FrameStep {
-  V6<double> S, U, V, Ap, F;
+  V3<double> ax;         // the 1-dof joint's axis
+  V3<double> at;         // the joint's origin; with own origins from the parent's (a root: zero)
+  V6<double> U, V, Ap, F;
   double Di;
   V3<double> mc;
   Sy3<double> I;
   double q, qd;          // 1-dof joint
-  V6<double> abase;      // free root: acceleration; ball: [acceleration, o]
+  V6<double> abase;      // free root: acceleration; ball: [acceleration, 0]
   // ball joint
   M3<double> R, B;       // pose; the articulated inertia's coupling block about o
   Sy3<double> Ai;        // inverse of its angular block
@@ -106,16 +151,16 @@ struct RootF {
 };
 __device__ __forceinline__ void root_pack(FrameStep& o, const RootF& f) {
   const double* L = f.L;
-  o.S = v6<double>(v3<double>(L[0], L[1], L[2]), v3<double>(L[3], L[4], L[5]));
-  o.U = v6<double>(v3<double>(L[6], L[7], L[8]), v3<double>(L[9], L[10], L[11]));
-  o.Di = L[12];
-  o.Ap = v6<double>(v3<double>(L[13], L[14], f.iv[0]), v3<double>(f.iv[1], f.iv[2], f.iv[3]));
-  o.F = v6<double>(v3<double>(f.iv[4], f.iv[5], 0.0), zero3<double>());
+  o.ax = v3<double>(L[0], L[1], L[2]);
+  o.U = v6<double>(v3<double>(L[3], L[4], L[5]), v3<double>(L[6], L[7], L[8]));
+  o.Di = L[9];
+  o.Ap = v6<double>(v3<double>(L[10], L[11], L[12]), v3<double>(L[13], L[14], f.iv[0]));
+  o.F = v6<double>(v3<double>(f.iv[1], f.iv[2], f.iv[3]), v3<double>(f.iv[4], f.iv[5], 0.0));
 }
 __device__ __forceinline__ RootF root_unpack(const FrameStep& o) {
-  return {{o.S.a.x, o.S.a.y, o.S.a.z, o.S.l.x, o.S.l.y, o.S.l.z, o.U.a.x, o.U.a.y, o.U.a.z, o.U.l.x, o.U.l.y,
-           o.U.l.z, o.Di, o.Ap.a.x, o.Ap.a.y},
-          {o.Ap.a.z, o.Ap.l.x, o.Ap.l.y, o.Ap.l.z, o.F.a.x, o.F.a.y}};
+  return {{o.ax.x, o.ax.y, o.ax.z, o.U.a.x, o.U.a.y, o.U.a.z, o.U.l.x, o.U.l.y, o.U.l.z, o.Di, o.Ap.a.x, o.Ap.a.y,
+           o.Ap.a.z, o.Ap.l.x, o.Ap.l.y},
+          {o.Ap.l.z, o.F.a.x, o.F.a.y, o.F.a.z, o.F.l.x, o.F.l.y}};
 }
 __device__ __forceinline__ RootF root_factor(const SySp<double>& IA) {
   double M[36];
@@ -150,18 +195,20 @@ __device__ __forceinline__ V6<double> root_solve(const RootF& f, const V6<double
   return v6<double>(v3<double>(r[0], r[1], r[2]), v3<double>(r[3], r[4], r[5]));
 }
 
-// a symmetric spatial inertia, and a force, moved from the base's origin to o
-__device__ __forceinline__ SySp<double> about(const SySp<double>& M, const V3<double>& o) {
-  // X = [1 0; [o]x 1] maps motions about o to the base's: M' = X^T M X
-  M3<double> E;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) E.m[k] = k % 4 == 0 ? 1.0 : 0.0;
-  return congruence_XT(E, -o, M);
+// The step from the parent's origin to the link's, and the joint's origin o:
+// one of the two is zero (which folds).
+template <typename S>
+__device__ __forceinline__ V3<double> step_of(const FrameLane<S>&, const FrameStep& o) {
+  return kOwnOrigin<S> ? o.at : zero3<double>();
 }
-__device__ __forceinline__ V3<double> moment_at(const V6<double>& f, const V3<double>& o) { return f.a - cross(o, f.l); }
-// [n about o; f] about the base's origin
-__device__ __forceinline__ V6<double> from_point(const V3<double>& n, const V3<double>& f, const V3<double>& o) {
-  return v6<double>(n + cross(o, f), f);
+template <typename S>
+__device__ __forceinline__ V3<double> joint_of(const FrameLane<S>&, const FrameStep& o) {
+  return kOwnOrigin<S> ? zero3<double>() : o.at;
+}
+// the 1-dof joint's motion subspace
+template <typename S>
+__device__ __forceinline__ V6<double> subspace(const FrameLane<S>& p, const FrameStep& o) {
+  return p.prism ? v6<double>(zero3<double>(), o.ax) : v6<double>(o.ax, cross(joint_of(p, o), o.ax));
 }
 
 // half: called half way, by every lane
@@ -180,17 +227,15 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
   M3<double> R;
 #pragma unroll
   for (int k = 0; k < 9; ++k) R.m[k] = k % 4 == 0 ? 1.0 : 0.0;
+  // the joint's origin from the parent's; own origins: in the link's axes
   V3<double> org = z3;
   const V3<double> grav = widen<double>(p.g);
   V3<double> gb = grav;
   const M3<double> ETt = widen<double>(transpose(p.L.ET));
   const double m = double(p.L.m);
   if (p.one) {
-    org = widen<double>(p.L.rT);
     R = ETt;
-    if (p.prism) {
-      org = axpy(org, o.q, col(ETt, 2));
-    } else {
+    if (!p.prism) {
       double sn, cs;
       sincos(o.q, &sn, &cs);
       // E_T^T times the rotation by q about z
@@ -200,10 +245,11 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
         R.m[3 * i + 1] = cs * ETt.m[3 * i + 1] - sn * ETt.m[3 * i];
       }
     }
+    org = widen<double>(p.L.rT);
+    if (p.prism) org = axpy(org, o.q, col(ETt, 2));
   }
   if constexpr (BALL) {
     if (p.ball) {
-      org = widen<double>(p.L.rT);
       const Q4<double> q = st_ball_quat(st);
       M3<double> Q;
 #pragma unroll
@@ -214,8 +260,11 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
         Q.m[6 + j] = c.z;
       }
       R = mul(ETt, Q);
+      org = widen<double>(p.L.rT);
     }
   }
+  if (p.par < 0) org = z3;  // where a fixed base stands does not matter
+  if constexpr (kOwnOrigin<S>) org = mulT(R, org);
 #pragma unroll
   for (int r = 0; r < kJumps; ++r) {
     if (1 << r > p.maxd) break;
@@ -228,30 +277,30 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
       M3<double> Rp;
 #pragma unroll
       for (int k = 0; k < 9; ++k) Rp.m[k] = u[k];
-      org = v3<double>(u[9], u[10], u[11]) + mul(Rp, org);
+      if constexpr (!kOwnOrigin<S>) org = v3<double>(u[9], u[10], u[11]) + mul(Rp, org);
       R = mul(Rp, R);
     }
     wave_sync();
   }
   // ---- velocities and bias accelerations (a free root's in the frame that
   // moves with its linear velocity, an exact shift)
-  const V3<double> ax = col(R, 2);
-  o.S = zero6<double>();
+  o.ax = col(R, 2);
+  if constexpr (kOwnOrigin<S>) o.at = mul(R, org);
+  else o.at = org;
+  const V3<double> sh = step_of(p, o), oj = joint_of(p, o);
+  const V6<double> Sj = subspace(p, o);
   V6<double> vJ = zero6<double>();
-  if (p.one) {
-    o.S = p.prism ? v6<double>(z3, ax) : v6<double>(ax, cross(org, ax));
-    vJ = o.qd * o.S;
-  }
+  if (p.one) vJ = o.qd * Sj;
   if constexpr (BALL) {
     if (p.ball) {
       const V3<double> w = mul(R, st_ball_w(st));
-      vJ = v6<double>(w, cross(org, w));
+      vJ = v6<double>(w, cross(oj, w));
     }
   }
   if constexpr (FREE) {
     if (p.root) vJ = v6<double>(st_vel6(st).a, z3);
   }
-  o.V = path_sum(p, vJ, xb);
+  o.V = path_sum(p, vJ, sh, xb);
   if constexpr (FREE) {
     // gravity in the root's frame, for its whole system
     const V3<double> gr = quat_rotate_T(st_quat(st), grav);
@@ -260,17 +309,17 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
     if (p.base >= 0) gb = t;
   }
   const V6<double> cb = p.root ? zero6<double>() : crm(o.V, vJ);
-  const V6<double> A0 = path_sum(p, cb, xb) - v6<double>(z3, gb);
-  // ---- inertia about the base's origin, bias force
+  const V6<double> A0 = path_sum(p, cb, sh, xb) - v6<double>(z3, gb);
+  // ---- inertia, bias force
   const V3<double> Rmc = mul(R, widen<double>(p.L.mc));
-  o.mc = axpy(Rmc, m, org);
+  o.mc = axpy(Rmc, m, oj);
   {
-    // I + [terms of the shift by org]: (2 org.Rmc + m org^2) 1 - sym(org, Rmc) ...
+    // I + [terms of the shift by o]: (2 o.Rmc + m o^2) 1 - sym(o, Rmc) ...
     const Sy3<double> J = cong(R, widen<double>(p.L.Ib));
-    const double d = dot(org, Rmc) + dot(org, o.mc);
-    o.I = sy3<double>(J.xx + d - (org.x * Rmc.x + o.mc.x * org.x), J.yy + d - (org.y * Rmc.y + o.mc.y * org.y),
-                      J.zz + d - (org.z * Rmc.z + o.mc.z * org.z), J.xy - (org.x * Rmc.y + o.mc.x * org.y),
-                      J.xz - (org.x * Rmc.z + o.mc.x * org.z), J.yz - (org.y * Rmc.z + o.mc.y * org.z));
+    const double t = dot(oj, Rmc) + dot(oj, o.mc);
+    o.I = sy3<double>(J.xx + t - (oj.x * Rmc.x + o.mc.x * oj.x), J.yy + t - (oj.y * Rmc.y + o.mc.y * oj.y),
+                      J.zz + t - (oj.z * Rmc.z + o.mc.z * oj.z), J.xy - (oj.x * Rmc.y + o.mc.x * oj.y),
+                      J.xz - (oj.x * Rmc.z + o.mc.x * oj.z), J.yz - (oj.y * Rmc.z + o.mc.y * oj.z));
   }
   LinkC<double> body;  // inertia_mul's view of it
   body.m = m;
@@ -298,26 +347,24 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
         F = F + Fc;
       }
       if (p.one) {
-        o.U = mul(IA, o.S);
-        o.Di = fast_rcp(dot(o.S, o.U));
-        u = ctl.x - dot(o.S, F);
-        if (p.par >= 0) {
-          put27(xb, p.lane, rank1_down(IA, o.U, o.Di), F + (u * o.Di) * o.U);
-        }
+        o.U = mul(IA, Sj);
+        o.Di = fast_rcp(dot(Sj, o.U));
+        u = ctl.x - dot(Sj, F);
+        if (p.par >= 0) put27(xb, p.lane, up(sh, rank1_down(IA, o.U, o.Di)), up(sh, F + (u * o.Di) * o.U));
       }
       if constexpr (BALL) {
         if (p.ball) {
-          const SySp<double> Io = about(IA, org);
+          const SySp<double> Io = up(-oj, IA);
           o.Ai = sy3_inv(Io.A);
           o.B = Io.B;
-          ub = tb - moment_at(F, org);
+          ub = tb - up(-oj, F).a;
           yb = mul(o.Ai, ub);
           if (p.par >= 0) {
             const M3<double> W = mul(sy_to_m3(o.Ai), o.B);
             const M3<double> BW = mul(transpose(o.B), W);
             SySp<double> Ia = zero_sysp<double>();
             Ia.C = Io.C - sy3<double>(BW.m[0], BW.m[4], BW.m[8], BW.m[1], BW.m[2], BW.m[5]);
-            put27(xb, p.lane, about(Ia, -org), from_point(tb, F.l + mulT(o.B, yb), org));
+            put27(xb, p.lane, up(sh + oj, Ia), up(sh + oj, v6<double>(tb, F.l + mulT(o.B, yb))));
           }
         }
       }
@@ -338,18 +385,16 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
   }
   for (int d = 0; d <= p.maxd; ++d) {
     if (p.dep == d) {
-      if (p.par >= 0) ap = get6(xb, 0, p.par);
+      if (p.par >= 0) ap = down(sh, get6(xb, 0, p.par));
       if (p.one) {
         qdd = (u - dot(o.U, ap)) * o.Di;
-        a = ap + qdd * o.S;
+        a = ap + qdd * Sj;
       }
       if constexpr (BALL) {
         if (p.ball) {
-          const V3<double> lo = ap.l + cross(ap.a, org);
-          const V3<double> Wl = mul(o.Ai, mul(o.B, lo)), al = yb - Wl;
-          const V3<double> acc = mulT(R, al - ap.a);  // in link coordinates, as the rate
-          a = v6<double>(al, lo - cross(al, org));
-          o.abase = v6<double>(acc, org);
+          const V3<double> lo = down(oj, ap).l, al = yb - mul(o.Ai, mul(o.B, lo));
+          a = down(-oj, v6<double>(al, lo));
+          o.abase = v6<double>(mulT(R, al - ap.a), z3);  // in link coordinates, as the rate
         }
       }
       if (p.cc) put6(xb, 0, p.lane, a);
@@ -371,21 +416,21 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
 template <bool FREE, bool BALL, typename S>
 __device__ __forceinline__ void frame_solve(const FrameLane<S>& p, const FrameStep& o, double& r, V3<double>& r3,
                                             V6<double>& r6, V6<double>& B, V6<double>& Bp, double* xb) {
-  const V3<double> org = o.abase.l;  // ball lanes
+  const V6<double> Sj = subspace(p, o);
+  const V3<double> sh = step_of(p, o), oj = joint_of(p, o);
   V3<double> y3 = zero3<double>();
   for (int d = p.maxd; d >= 0; --d) {
     if (p.dep == d) {
       V6<double> s = zero6<double>();
       for (int c = 0; c < p.cc; ++c) s = s + get6(xb, 0, p.cf + c);
       if (p.one) {
-        r = r - dot(o.S, s);
-        if (p.par >= 0) put6(xb, 0, p.lane, s + (r * o.Di) * o.U);
+        r = r - dot(Sj, s);
+        if (p.par >= 0) put6(xb, 0, p.lane, up(sh, s + (r * o.Di) * o.U));
       }
       if constexpr (BALL) {
         if (p.ball) {
-          const V3<double> r0 = r3;
-          y3 = mul(o.Ai, r0 - moment_at(s, org));
-          if (p.par >= 0) put6(xb, 0, p.lane, from_point(r0, s.l + mulT(o.B, y3), org));
+          y3 = mul(o.Ai, r3 - up(-oj, s).a);
+          if (p.par >= 0) put6(xb, 0, p.lane, up(sh + oj, v6<double>(r3, s.l + mulT(o.B, y3))));
         }
       }
       if constexpr (FREE) {
@@ -403,17 +448,16 @@ __device__ __forceinline__ void frame_solve(const FrameLane<S>& p, const FrameSt
   }
   for (int d = 0; d <= p.maxd; ++d) {
     if (p.dep == d) {
-      if (p.par >= 0) Bp = get6(xb, 0, p.par);
+      if (p.par >= 0) Bp = down(sh, get6(xb, 0, p.par));
       if (p.one) {
         r = (r - dot(o.U, Bp)) * o.Di;
-        B = Bp + r * o.S;
+        B = Bp + r * Sj;
       }
       if constexpr (BALL) {
         if (p.ball) {
-          const V3<double> lo = Bp.l + cross(Bp.a, org);
-          const V3<double> al = y3 - mul(o.Ai, mul(o.B, lo));
+          const V3<double> lo = down(oj, Bp).l, al = y3 - mul(o.Ai, mul(o.B, lo));
           r3 = al - Bp.a;
-          B = v6<double>(al, lo - cross(al, org));
+          B = down(-oj, v6<double>(al, lo));
         }
       }
       if (p.cc) put6(xb, 0, p.lane, B);
@@ -469,8 +513,8 @@ __device__ __forceinline__ V3<double> frame_reverse(const FrameLane<S>& p, const
         e = e + get6(xb, 6, p.cf + c);
       }
       if (p.par >= 0) {
-        put6(xb, 0, p.lane, G);
-        put6(xb, 6, p.lane, e);
+        put6(xb, 0, p.lane, up(step_of(p, o), G));
+        put6(xb, 6, p.lane, up(step_of(p, o), e));
       }
     }
     wave_sync();
@@ -478,21 +522,21 @@ __device__ __forceinline__ V3<double> frame_reverse(const FrameLane<S>& p, const
   // ---- the subtree turns with q: what enters it from the parent turns back
   V3<double> taub = zero3<double>();
   if (p.one) {
-    const V6<double> Vp = o.V - o.qd * o.S;
+    const V6<double> Sj = subspace(p, o), Vp = o.V - o.qd * Sj;
     const V6<double> vb = e + crmT(Vp, G);
-    const double qE = dot(o.S, crf(Bp, o.F) + crf(o.Ap, G) + crf(Vp, vb));
-    const double qdE = dot(o.S, crmT(o.V, G) + vb);
+    const double qE = dot(Sj, crf(Bp, o.F) + crf(o.Ap, G) + crf(Vp, vb));
+    const double qdE = dot(Sj, crmT(o.V, G) + vb);
     x1.q[0] = x1.q[0] + qE + lq * r;
     x1.qd[0] = tot - qdE + lqd * r;
     taub.x = r;
   }
   if constexpr (BALL) {
     if (p.ball) {
-      const V3<double> org = o.abase.l, w = mul(o.R, st_ball_w(st));
-      const V6<double> Vp = o.V - v6<double>(w, cross(org, w));
+      const V3<double> oj = joint_of(p, o), w = mul(o.R, st_ball_w(st));
+      const V6<double> Vp = o.V - v6<double>(w, cross(oj, w));
       const V6<double> vb = e + crmT(Vp, G);
-      const V3<double> turn = mulT(o.R, moment_at(crf(Bp, o.F) + crf(o.Ap, G) + crf(Vp, vb), org));
-      const V3<double> rate = mulT(o.R, moment_at(crmT(o.V, G) + vb, org));
+      const V3<double> turn = mulT(o.R, up(-oj, crf(Bp, o.F) + crf(o.Ap, G) + crf(Vp, vb)).a);
+      const V3<double> rate = mulT(o.R, up(-oj, crmT(o.V, G) + vb).a);
       const Q4<double> t = ball_quat_bar(st_ball_quat(st), turn);
       x1.q[0] = qb.x + t.x;
       x1.q[1] = qb.y + t.y;
@@ -578,7 +622,7 @@ __device__ __forceinline__ void frame_fields(FrameStep& o, F&& f) {
   auto w3 = [&](V3<double>& v) { w(v.x); w(v.y); w(v.z); };
   auto w6 = [&](V6<double>& v) { w3(v.a); w3(v.l); };
   auto ws = [&](Sy3<double>& m) { w(m.xx); w(m.yy); w(m.zz); w(m.xy); w(m.xz); w(m.yz); };
-  w6(o.S); w6(o.U); w6(o.V); w6(o.Ap); w6(o.F);
+  w3(o.ax); w3(o.at); w6(o.U); w6(o.V); w6(o.Ap); w6(o.F);
   w(o.Di);
   w3(o.mc);
   ws(o.I);
