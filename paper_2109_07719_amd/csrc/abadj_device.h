@@ -1701,7 +1701,10 @@ hipError_t launch_backward_p(const BwdArgs<S>& a, const Tiling& tl, hipStream_t 
     if (a.K != 0) return launch_backward_planar(a, tl, st);
     return launch_backward_one<S, R, F, E, C, PARAMS>(a, tl, st);
   } else if constexpr (!PARAMS && sizeof(R) == sizeof(double)) {
-    if (a.K != 0) return launch_backward_frame<S, F, E, C>(a, tl, st);
+    // the base frame's formulas take joint frames for rotations, the reversed
+    // statements any matrix: with frames off by more than their own rounding
+    // (an FP64 handle with FP32 frames, say) only those are the step's gradient
+    if (a.K != 0 && a.P.rotations) return launch_backward_frame<S, F, E, C>(a, tl, st);
     return launch_backward_one<S, R, F, E, C, PARAMS>(a, tl, st);
   } else if (a.K == 1 && tl.pipelined) {
     const size_t per = pipe_lds_per_pair<S, R, F, E, C>();

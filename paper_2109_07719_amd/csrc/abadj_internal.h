@@ -42,6 +42,7 @@ struct Packed {
   int nq, nv, nu;        // totals over the batch
   unsigned long long* status;  // device counter of non-finite numbers written to outputs
   int has_limits;        // some joint has limits (CF_LIM)
+  int rotations;         // every joint frame is a rotation, to the roundings of the type
 };
 
 template <typename S>

@@ -49,6 +49,7 @@ struct sim_handle {
   int nwaves = 0, nslots = 0, max_depth = 0, nfree = 0, mfree = 0;
   bool has_free = false;
   bool eti = false;  // every joint frame is the identity after canonicalisation
+  bool rotations = true;  // every joint frame is a rotation as far as the dtype shows
   bool chain = false;  // every system is a fixed-base serial chain of revolute joints
   bool has_prism = false;  // some joint is prismatic
   bool has_limits = false;  // joint limits were given
@@ -124,6 +125,7 @@ aba::Packed<S> packed(const sim_handle* h) {
   P.nv = h->nv;
   P.nu = h->nu;
   P.has_limits = h->has_limits ? 1 : 0;
+  P.rotations = h->rotations ? 1 : 0;
   return P;
 }
 
@@ -521,8 +523,17 @@ int sim_create(const sim_topology* topo, const sim_params* prm, int dtype, sim_t
       mat3_mul(Rl, J, T2);
       mat3_mul_bt(T2, Rl, Jn);
       const double I[6] = {Jn[0], Jn[4], Jn[8], Jn[1], Jn[2], Jn[5]};
-      if (topo->jtype[L] != SIM_JOINT_FREE)
+      if (topo->jtype[L] != SIM_JOINT_FREE) {
         for (int k = 0; k < 9; ++k) eti = eti && std::fabs(ETn[k] - I3[k]) < 1e-12;
+        // the roundings of a rotation's own entries, and some, in the handle's type
+        double G[9];
+        mat3_mul_bt(ETn, ETn, G);
+        for (int k = 0; k < 9; ++k)
+          h->rotations = h->rotations && std::fabs(G[k] - I3[k]) < (dtype == SIM_F64 ? 1e-14 : 3e-7);
+        h->rotations = h->rotations && ETn[0] * (ETn[4] * ETn[8] - ETn[5] * ETn[7]) +
+                                               ETn[1] * (ETn[5] * ETn[6] - ETn[3] * ETn[8]) +
+                                               ETn[2] * (ETn[3] * ETn[7] - ETn[4] * ETn[6]) > 0;
+      }
       CF(aba::CF_M) = m;
       for (int k = 0; k < 3; ++k) CF(aba::CF_MC + k) = m * c[k];
       // inertia about the link origin: Ic - m [c]x^2 = Ic + m (|c|^2 1 - c c^T)

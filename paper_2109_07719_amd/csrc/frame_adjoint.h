@@ -27,7 +27,10 @@
 //
 // A ball joint's three axes turn with its link; its subspace is every
 // rotation about the joint's origin o, S = [1; [o]x], and its block form is
-// taken about o, where S = [1; 0] (aba_lane.h, "ball joint").
+// taken about o, where S = [1; 0] (aba_lane.h, "ball joint").  A quaternion off
+// the unit sphere scales the joint's transform by |quat|^2 (as the step does):
+// the pose takes the rotation alone, and whatever passes through the joint,
+// motions down and forces up, is multiplied.
 #pragma once
 
 #include "planar_adjoint.h"
@@ -103,25 +106,31 @@ __device__ __forceinline__ SySp<double> up(const V3<double>& d, const SySp<doubl
 // Motions v of the link and its ancestors summed, about the link's origin: by
 // doubling rounds through the exchange records (a round: one write and one
 // read of every lane).  With own origins a round also carries the step D over
-// the links summed so far.
-template <typename S>
-__device__ __forceinline__ V6<double> path_sum(const FrameLane<S>& p, V6<double> v, V3<double> D, double* xb) {
+// the links summed so far, with ball joints the scale of their transforms
+// (returned: the whole path's).
+template <bool BALL, typename S>
+__device__ __forceinline__ V6<double> path_sum(const FrameLane<S>& p, V6<double> v, V3<double> D, double& scale,
+                                               double* xb) {
 #pragma unroll
   for (int r = 0; r < kJumps; ++r) {
     if (1 << r > p.maxd) break;
     put6(xb, 0, p.lane, v);
-    if constexpr (kOwnOrigin<S>) {
-      const double t[4] = {D.x, D.y, D.z, 0.0};
+    if constexpr (kOwnOrigin<S> || BALL) {
+      const double t[4] = {D.x, D.y, D.z, scale};
       put_rec(xb, p.lane, 6, t);
     }
     wave_sync();
     if (p.anc[r] >= 0) {
       V6<double> u = get6(xb, 0, p.anc[r]);
-      if constexpr (kOwnOrigin<S>) {
+      if constexpr (kOwnOrigin<S> || BALL) {
         double t[4];
         get_rec(xb, p.anc[r], 6, t);
         u = down(D, u);
         D = v3<double>(t[0], t[1], t[2]) + D;
+        if constexpr (BALL) {
+          u = scale * u;
+          scale *= t[3];
+        }
       }
       v = u + v;
     }
@@ -140,7 +149,7 @@ struct FrameStep {
   V3<double> mc;
   Sy3<double> I;
   double q, qd;          // 1-dof joint
-  V6<double> abase;      // free root: acceleration; ball: [acceleration, 0]
+  V6<double> abase;      // free root: acceleration; ball: [acceleration, (|quat|^2, 0, 0)]
   // ball joint
   M3<double> R, B;       // pose; the articulated inertia's coupling block about o
   Sy3<double> Ai;        // inverse of its angular block
@@ -218,6 +227,11 @@ template <typename S>
 __device__ __forceinline__ V3<double> joint_of(const FrameLane<S>&, const FrameStep& o) {
   return kOwnOrigin<S> ? zero3<double>() : o.at;
 }
+// the scale of the joint's transform
+template <bool BALL, typename S>
+__device__ __forceinline__ double scale_of(const FrameLane<S>& p, const FrameStep& o) {
+  return BALL && p.ball ? o.abase.l.x : 1.0;
+}
 // the 1-dof joint's motion subspace
 template <typename S>
 __device__ __forceinline__ V6<double> subspace(const FrameLane<S>& p, const FrameStep& o) {
@@ -264,10 +278,12 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
   if constexpr (BALL) {
     if (p.ball) {
       const Q4<double> q = st_ball_quat(st);
+      const double qq = q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
+      o.abase.l.x = qq;
       M3<double> Q;
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        const V3<double> c = quat_rotate(q, v3<double>(double(j == 0), double(j == 1), double(j == 2)));
+        const V3<double> c = (1.0 / qq) * quat_rotate(q, v3<double>(double(j == 0), double(j == 1), double(j == 2)));
         Q.m[j] = c.x;
         Q.m[3 + j] = c.y;
         Q.m[6 + j] = c.z;
@@ -303,6 +319,7 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
   if constexpr (kOwnOrigin<S>) o.at = mul(R, org);
   else o.at = org;
   const V3<double> sh = step_of(p, o), oj = joint_of(p, o);
+  const double ks = scale_of<BALL>(p, o);
   const V6<double> Sj = subspace(p, o);
   V6<double> vJ = zero6<double>();
   if (p.one) vJ = o.qd * Sj;
@@ -315,7 +332,8 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
   if constexpr (FREE) {
     if (p.root) vJ = v6<double>(st_vel6(st).a, z3);
   }
-  o.V = path_sum(p, vJ, sh, xb);
+  double path = ks;
+  o.V = path_sum<BALL>(p, vJ, sh, path, xb);
   if constexpr (FREE) {
     // gravity in the root's frame, for its whole system
     const V3<double> gr = quat_rotate_T(st_quat(st), grav);
@@ -324,7 +342,8 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
     if (p.base >= 0) gb = t;
   }
   const V6<double> cb = p.root ? zero6<double>() : crm(o.V, vJ);
-  const V6<double> A0 = path_sum(p, cb, sh, xb) - v6<double>(z3, gb);
+  double kp = ks;
+  const V6<double> A0 = path_sum<BALL>(p, cb, sh, kp, xb) - v6<double>(z3, BALL ? path * gb : gb);
   // ---- inertia, bias force
   const V3<double> Rmc = mul(R, widen<double>(p.L.mc));
   o.mc = axpy(Rmc, m, oj);
@@ -379,7 +398,9 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
             const M3<double> BW = mul(transpose(o.B), W);
             SySp<double> Ia = zero_sysp<double>();
             Ia.C = Io.C - sy3<double>(BW.m[0], BW.m[4], BW.m[8], BW.m[1], BW.m[2], BW.m[5]);
-            put27(xb, p.lane, up(sh + oj, Ia), up(sh + oj, v6<double>(tb, F.l + mulT(o.B, yb))));
+            Ia.C = sy3<double>(ks * ks * Ia.C.xx, ks * ks * Ia.C.yy, ks * ks * Ia.C.zz, ks * ks * Ia.C.xy,
+                               ks * ks * Ia.C.xz, ks * ks * Ia.C.yz);
+            put27(xb, p.lane, up(sh + oj, Ia), ks * up(sh + oj, v6<double>(tb, F.l + mulT(o.B, yb))));
           }
         }
       }
@@ -401,6 +422,7 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
   for (int d = 0; d <= p.maxd; ++d) {
     if (p.dep == d) {
       if (p.par >= 0) ap = down(sh, get6(xb, 0, p.par));
+      if constexpr (BALL) ap = ks * ap;
       if (p.one) {
         qdd = (u - dot(o.U, ap)) * o.Di;
         a = ap + qdd * Sj;
@@ -409,7 +431,7 @@ __device__ __forceinline__ FrameStep frame_recompute(const FrameLane<S>& p, cons
         if (p.ball) {
           const V3<double> lo = down(oj, ap).l, al = yb - mul(o.Ai, mul(o.B, lo));
           a = down(-oj, v6<double>(al, lo));
-          o.abase = v6<double>(mulT(R, al - ap.a), z3);  // in link coordinates, as the rate
+          o.abase.a = mulT(R, al - ap.a);  // in link coordinates, as the rate
         }
       }
       if (p.cc) put6(xb, 0, p.lane, a);
@@ -433,6 +455,7 @@ __device__ __forceinline__ void frame_solve(const FrameLane<S>& p, const FrameSt
                                             V6<double>& r6, V6<double>& B, V6<double>& Bp, double* xb) {
   const V6<double> Sj = subspace(p, o);
   const V3<double> sh = step_of(p, o), oj = joint_of(p, o);
+  const double ks = scale_of<BALL>(p, o);
   V3<double> y3 = zero3<double>();
   for (int d = p.maxd; d >= 0; --d) {
     if (p.dep == d) {
@@ -445,7 +468,7 @@ __device__ __forceinline__ void frame_solve(const FrameLane<S>& p, const FrameSt
       if constexpr (BALL) {
         if (p.ball) {
           y3 = mul(o.Ai, r3 - up(-oj, s).a);
-          if (p.par >= 0) put6(xb, 0, p.lane, up(sh + oj, v6<double>(r3, s.l + mulT(o.B, y3))));
+          if (p.par >= 0) put6(xb, 0, p.lane, ks * up(sh + oj, v6<double>(r3, s.l + mulT(o.B, y3))));
         }
       }
       if constexpr (FREE) {
@@ -464,6 +487,7 @@ __device__ __forceinline__ void frame_solve(const FrameLane<S>& p, const FrameSt
   for (int d = 0; d <= p.maxd; ++d) {
     if (p.dep == d) {
       if (p.par >= 0) Bp = down(sh, get6(xb, 0, p.par));
+      if constexpr (BALL) Bp = ks * Bp;
       if (p.one) {
         r = (r - dot(o.U, Bp)) * o.Di;
         B = Bp + r * Sj;
@@ -514,22 +538,34 @@ __device__ __forceinline__ V3<double> frame_reverse(const FrameLane<S>& p, const
   frame_solve<FREE, BALL>(p, o, r, r3, r6, B, Bp, xb);
   // ---- <w, ID> = sum_i B_i . (I A + V x* I V): per link its share of A's
   // adjoint, I B, and of V's (the bias accelerations V_l x S_l qd_l from the
-  // root to link i sum to V_i in the second), summed over subtrees
+  // root to link i sum to V_i in the second), summed over subtrees.  Scaled
+  // transforms don't let them: with ball joints they are taken link by link
   LinkC<double> body;
   body.m = double(p.L.m);
   body.mc = o.mc;
   body.Ib = o.I;
   V6<double> G = inertia_mul(body, B);
-  V6<double> e = crmT(B, inertia_mul(body, o.V)) - inertia_mul(body, crm(o.V, B)) - crmT(o.V, G);
+  V6<double> e = crmT(B, inertia_mul(body, o.V)) - inertia_mul(body, crm(o.V, B)), vJ = zero6<double>();
+  if constexpr (BALL) {
+    if (p.one) vJ = o.qd * subspace(p, o);
+    if (p.ball) {
+      const V3<double> w = mul(o.R, st_ball_w(st));
+      vJ = v6<double>(w, cross(joint_of(p, o), w));
+    }
+  } else {
+    e = e - crmT(o.V, G);
+  }
   for (int d = p.maxd; d >= 0; --d) {
     if (p.dep == d) {
       for (int c = 0; c < p.cc; ++c) {
         G = G + get6(xb, 0, p.cf + c);
         e = e + get6(xb, 6, p.cf + c);
       }
+      if constexpr (BALL) e = e - crmT(vJ, G);
       if (p.par >= 0) {
-        put6(xb, 0, p.lane, up(step_of(p, o), G));
-        put6(xb, 6, p.lane, up(step_of(p, o), e));
+        const double ks = scale_of<BALL>(p, o);
+        put6(xb, 0, p.lane, BALL ? ks * up(step_of(p, o), G) : up(step_of(p, o), G));
+        put6(xb, 6, p.lane, BALL ? ks * up(step_of(p, o), e) : up(step_of(p, o), e));
       }
     }
     wave_sync();
@@ -538,7 +574,7 @@ __device__ __forceinline__ V3<double> frame_reverse(const FrameLane<S>& p, const
   V3<double> taub = zero3<double>();
   if (p.one) {
     const V6<double> Sj = subspace(p, o), Vp = o.V - o.qd * Sj;
-    const V6<double> vb = e + crmT(Vp, G);
+    const V6<double> vb = BALL ? e : e + crmT(Vp, G);
     const double qE = dot(Sj, crf(Bp, o.F) + crf(o.Ap, G) + crf(Vp, vb));
     const double qdE = dot(Sj, crmT(o.V, G) + vb);
     x1.q[0] = x1.q[0] + qE + lq * r;
@@ -547,11 +583,9 @@ __device__ __forceinline__ V3<double> frame_reverse(const FrameLane<S>& p, const
   }
   if constexpr (BALL) {
     if (p.ball) {
-      const V3<double> oj = joint_of(p, o), w = mul(o.R, st_ball_w(st));
-      const V6<double> Vp = o.V - v6<double>(w, cross(oj, w));
-      const V6<double> vb = e + crmT(Vp, G);
-      const V3<double> turn = mulT(o.R, up(-oj, crf(Bp, o.F) + crf(o.Ap, G) + crf(Vp, vb)).a);
-      const V3<double> rate = mulT(o.R, up(-oj, crmT(o.V, G) + vb).a);
+      const V3<double> oj = joint_of(p, o);
+      const V3<double> turn = mulT(o.R, up(-oj, crf(Bp, o.F) + crf(o.Ap, G) + crf(o.V - vJ, e)).a);
+      const V3<double> rate = mulT(o.R, up(-oj, crmT(o.V, G) + e).a);
       const Q4<double> t = ball_quat_bar(st_ball_quat(st), turn);
       x1.q[0] = qb.x + t.x;
       x1.q[1] = qb.y + t.y;
@@ -569,7 +603,7 @@ __device__ __forceinline__ V3<double> frame_reverse(const FrameLane<S>& p, const
       // [0; w x v] - [0; R^T g]
       const V6<double> v = st_vel6(st);
       const Q4<double> t = quat_rot_grad(st_quat(st), widen<double>(p.g), G.l);
-      const V3<double> wv = g6.a - (e.a + crmT(o.V, G).a) - cross(v.l, G.l);
+      const V3<double> wv = g6.a - (BALL ? e.a : e.a + crmT(o.V, G).a) - cross(v.l, G.l);
       const V3<double> lv = g6.l - cross(G.l, v.a);
       x1.q[0] = pb.x;
       x1.q[1] = pb.y;
