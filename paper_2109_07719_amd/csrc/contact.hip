@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kWave) void k_contact_rollout(RollArgs<S> a) {
     const double u = un;
     if (l.one && t + 1 < a.T) un = double(a.tau[((size_t)(t + 1) * nu + l.ui) * B + s]);
     wave::Step o;
-    wave::step<false>(a.tp, l, g, x, u, a.dt, a.tp.mu, o);
+    wave::step<false, sizeof(S) == sizeof(double)>(a.tp, l, g, x, u, a.dt, a.tp.mu, o);
     wave::integrate(l, x, o, a.dt);
     wave::round_state<S>(x);
     if (a.ncont && live && l.gl == 0) a.ncont[(size_t)t * B + s] = o.na;
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kWave) void k_contact_adj(GradArgs<S> a) {
     const double u = un;
     if (t > 0) fetch(t - 1);
     wave::Step o;
-    wave::step<true>(a.tp, l, g, x, u, a.dt, a.tp.mu, o);
+    wave::step<true, sizeof(S) == sizeof(double)>(a.tp, l, g, x, u, a.dt, a.tp.mu, o);
     const double ub = wave::step_vjp(a.tp, l, g, x, a.dt, a.tp.mu, xb, mub, o);
     if (live && l.one) a.gtau[((size_t)t * nu + l.ui) * B + s] = S(ub);
   }
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(2 * kWave) void k_contact_adj_pair(GradArgs<S> a) {
       x = nxt;
       const double u = un;
       fetch(t - 3);
-      wave::step<true>(a.tp, l, g, x, u, a.dt, a.tp.mu, o);
+      wave::step<true, sizeof(S) == sizeof(double)>(a.tp, l, g, x, u, a.dt, a.tp.mu, o);
     }
     __syncthreads();
   }
