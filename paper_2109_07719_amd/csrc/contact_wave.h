@@ -256,6 +256,17 @@ __device__ __forceinline__ SySp<D> up(const V3<D>& d, const SySp<D>& M) {
   return aba::congruence_XT(E, d, M);
 }
 
+// The rotation nearest to R by a Newton step, R (3 - R^T R) / 2: the gradient
+// takes every pose for a rotation, and a joint frame in FP32 is one only to
+// 6e-8 (two steps, once a launch: of matrices with a few digits, too).  Error of
+// tau_bar, one step of 8 to 16 links in contact, FP32: 1e-7 -> 4e-8.
+__device__ __forceinline__ M3<D> nearest_rotation(const M3<D>& R) {
+  M3<D> G = aba::mul(aba::transpose(R), R);
+#pragma unroll
+  for (int k = 0; k < 9; ++k) G.m[k] = (k % 4 == 0 ? 1.5 : 0.0) - 0.5 * G.m[k];
+  return aba::mul(R, G);
+}
+
 // One lane's constants: its link, and its contact row.
 struct Lane {
   int gl, p, dep, cf, ccn, jt, slot, dof, sub, sph;
@@ -298,6 +309,7 @@ __device__ __forceinline__ Lane load_lane(const WTopo& tp, const S* P, size_t B,
   for (int a = 0; a < 3; ++a)
 #pragma unroll
     for (int b = 0; b < 3; ++b) l.ETt.m[3 * b + a] = at(3 * a + b);
+  if (l.one) l.ETt = nearest_rotation(nearest_rotation(l.ETt));
   l.rT = aba::v3<D>(at(9), at(10), at(11));
   l.ax = aba::v3<D>(at(12), at(13), at(14));
   if (l.one) l.ax = (1.0 / sqrt(dot(l.ax, l.ax))) * l.ax;
