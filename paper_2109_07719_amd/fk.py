@@ -14,7 +14,8 @@ are rejected.
 On the GPU the positions and their adjoint come from one kernel each
 (`sim_link_points`), a point's path to the root composed by one wavefront;
 anything beyond a plain first-order call (CPU tensors, higher derivatives,
-forward mode, function transforms, tracing) runs the torch expressions.
+forward mode, function transforms, batched cotangents, tracing) runs the torch
+expressions.
 """
 from __future__ import annotations
 
@@ -65,6 +66,20 @@ def _paths(target, parent, jtype, most=_MAX_PATH):
     return np.where(k >= 0, np.take_along_axis(up, np.maximum(k, 0), axis=1), -1).astype(np.int32)
 
 
+def _plain(t):
+    """Whether t is an ordinary tensor outside every transform: one whose data
+    a kernel may read."""
+    if type(t) not in (torch.Tensor, torch.nn.Parameter):
+        return False
+    if torch.compiler.is_compiling() or torch.jit.is_tracing():
+        return False
+    F = torch._C._functorch
+    if F.peek_interpreter_stack() is not None or _get_current_dispatch_mode() is not None:
+        return False
+    # cotangents of is_grads_batched and jacobian(vectorize=True) come without an interpreter
+    return not F.is_legacy_batchedtensor(t) and fwad.unpack_dual(t).tangent is None
+
+
 class _Points(torch.autograd.Function):
     @staticmethod
     def forward(ctx, q, fk):
@@ -79,6 +94,11 @@ class _Points(torch.autograd.Function):
         q, *tables = ctx.saved_tensors
         if torch.is_grad_enabled():   # a graph of the gradient is wanted
             return torch.autograd.grad(ctx.fk._positions(q), q, g, create_graph=True)[0], None
+        if not _plain(g):
+            with torch.enable_grad():
+                v = q.detach().requires_grad_()
+                x = ctx.fk._positions(v)
+            return torch.autograd.grad(x, v, g)[0], None
         gq = torch.zeros_like(q)
         ctx.fk._call("sim_link_points_adjoint", q, *tables, g.contiguous(), gq)
         return gq, None
@@ -142,13 +162,7 @@ class LinkPoints(torch.nn.Module):
 
     def _native(self, q):
         """Whether a call on q is one the kernels take."""
-        if self._path is None or type(q) not in (torch.Tensor, torch.nn.Parameter) or q.dtype not in _DT:
-            return False
-        if torch.compiler.is_compiling() or torch.jit.is_tracing():
-            return False
-        if torch._C._functorch.peek_interpreter_stack() is not None or _get_current_dispatch_mode() is not None:
-            return False
-        if torch.is_autocast_enabled() or fwad.unpack_dual(q).tangent is not None:
+        if self._path is None or q.dtype not in _DT or not _plain(q) or torch.is_autocast_enabled():
             return False
         fits = lambda t, n: (type(t) is torch.Tensor and t.dtype == q.dtype and t.device == q.device
                              and t.numel() == n and t.is_contiguous() and not t.requires_grad)

@@ -1,0 +1,44 @@
+"""Calls of link points that a user makes beyond one gradient: Jacobians with
+batched cotangents."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2109_07719_amd import synth
+from paper_2109_07719_amd.fk import LinkPoints
+
+pytestmark = pytest.mark.gpu
+G = torch.device("cuda")
+
+
+def chains(k, n=5):
+    return [synth.chain_system(n, 20 + i, 1)[0] for i in range(k)]
+
+
+def points(k):
+    return np.random.default_rng(1).normal(size=(k, 3))
+
+
+def jacobian(fk, q):
+    """Row by row, by the torch expressions."""
+    v = q.detach().clone().requires_grad_()
+    x = fk._positions(v).reshape(-1)
+    return torch.stack([torch.autograd.grad(x[i], v, retain_graph=True)[0] for i in range(x.numel())])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_batched_cotangents(dtype):
+    fk = LinkPoints(chains(2), [4, 2], points(2), dtype=dtype)
+    q = torch.randn(10, dtype=dtype, device=G, requires_grad=True)
+    assert fk._native(q)
+    ref = jacobian(fk, q)
+    eye = torch.eye(6, dtype=dtype, device=G).reshape(6, 2, 3)
+    tol = dict(rtol=0, atol=40 * 5 * torch.finfo(dtype).eps * float(ref.abs().max()))
+    got, = torch.autograd.grad(fk(q), q, eye, is_grads_batched=True)
+    assert torch.allclose(got, ref, **tol)
+    J = torch.autograd.functional.jacobian(fk, q, vectorize=True)
+    assert torch.allclose(J.reshape(6, 10), ref, **tol)
+    assert torch.allclose(torch.autograd.functional.jacobian(fk, q).reshape(6, 10), ref, **tol)
+    assert torch.allclose(torch.func.jacrev(fk)(q.detach()).reshape(6, 10), ref, **tol)
+    assert torch.allclose(torch.func.jacfwd(fk)(q.detach()).reshape(6, 10), ref, **tol)
