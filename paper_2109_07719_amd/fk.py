@@ -179,7 +179,10 @@ class LinkPoints(torch.nn.Module):
                                            *(p(t) for t in last), _stream()))
 
     def forward(self, q):
-        return _Points.apply(q, self) if self._native(q) else self._positions(q)
+        if not self._native(q):
+            return self._positions(q)
+        # a copy for the adjoint: q may be changed in place after the call
+        return _Points.apply(q.clone() if q.requires_grad and torch.is_grad_enabled() else q, self)
 
     def _positions(self, q):
         n = self.n_links

@@ -1,5 +1,5 @@
 """Calls of link points that a user makes beyond one gradient: Jacobians with
-batched cotangents."""
+batched cotangents, a q changed in place after the call."""
 import numpy as np
 import pytest
 
@@ -42,3 +42,17 @@ def test_batched_cotangents(dtype):
     assert torch.allclose(torch.autograd.functional.jacobian(fk, q).reshape(6, 10), ref, **tol)
     assert torch.allclose(torch.func.jacrev(fk)(q.detach()).reshape(6, 10), ref, **tol)
     assert torch.allclose(torch.func.jacfwd(fk)(q.detach()).reshape(6, 10), ref, **tol)
+
+
+def test_q_may_change_in_place_after_the_call():
+    fk = LinkPoints(chains(2), [4, 2], points(2), dtype=torch.float64)
+    q = torch.randn(10, dtype=torch.float64, device=G)
+    g = torch.randn(2, 3, dtype=torch.float64, device=G)
+    v = q.clone().requires_grad_()
+    ref, = torch.autograd.grad(fk._positions(v), v, g)
+    leaf = q.clone().requires_grad_()
+    x = fk(leaf)
+    with torch.no_grad():
+        leaf += 1.0
+    x.backward(g)
+    assert torch.allclose(leaf.grad, ref, rtol=0, atol=1e-13)
