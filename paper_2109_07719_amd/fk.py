@@ -14,8 +14,8 @@ are rejected.
 On the GPU the positions and their adjoint come from one kernel each
 (`sim_link_points`), a point's path to the root composed by one wavefront;
 anything beyond a plain first-order call (CPU tensors, higher derivatives,
-forward mode, function transforms, batched cotangents, tracing) runs the torch
-expressions.
+forward mode, function transforms, batched cotangents, tracing) and points
+whose paths share a link run the torch expressions.
 """
 from __future__ import annotations
 
@@ -108,6 +108,8 @@ class LinkPoints(torch.nn.Module):
     """World positions of one point per system: point `pts[s]` (link
     coordinates) on link `links[s]` (local index) of system s."""
 
+    _path = None   # the points' paths on the GPU, if the kernels take them
+
     def __init__(self, systems, links, pts, dtype=torch.float32, device="cuda"):
         super().__init__()
         glob_par, dep, qidx, jt, ET, rT, ax, target = [], [], [], [], [], [], [], []
@@ -154,8 +156,9 @@ class LinkPoints(torch.nn.Module):
                            for d in range(int(self.depth.max()) + 1)]
 
         path = _paths(np.asarray(target), np.asarray(glob_par), self.jtype)
-        self._path = None
-        if path is not None and self.rT.is_cuda:
+        # the adjoint kernel writes each path's joints: no two may share one
+        on = [] if path is None else path[path >= 0]
+        if path is not None and np.unique(on).size == on.size and self.rT.is_cuda:
             self._path = torch.tensor(path, device=device)
             self._jtype = torch.tensor(self.jtype, dtype=torch.int32, device=device)
             self._nq = int(qbase)

@@ -1,5 +1,8 @@
 """Calls of link points that a user makes beyond one gradient: Jacobians with
-batched cotangents, a q changed in place after the call."""
+batched cotangents, a q changed in place after the call, points that share
+joints, a module stored by an earlier version."""
+import copy
+
 import numpy as np
 import pytest
 
@@ -56,3 +59,24 @@ def test_q_may_change_in_place_after_the_call():
         leaf += 1.0
     x.backward(g)
     assert torch.allclose(leaf.grad, ref, rtol=0, atol=1e-13)
+
+
+@pytest.mark.parametrize("links", [[4, -1], [9, 2], [-10, 0]])
+def test_points_that_share_joints_add_up(links):
+    """Indices that reach into the neighbouring system, as a negative one does."""
+    fk = LinkPoints(chains(2), links, points(2), dtype=torch.float64)
+    q = torch.randn(10, dtype=torch.float64, device=G, requires_grad=True)
+    g = torch.randn(2, 3, dtype=torch.float64, device=G)
+    x, ref = fk(q), fk._positions(q)
+    assert torch.allclose(x, ref, rtol=0, atol=1e-13)
+    (gq,), (gr,) = torch.autograd.grad(x, q, g), torch.autograd.grad(ref, q, g)
+    assert torch.allclose(gq, gr, rtol=0, atol=1e-13)
+
+
+def test_a_module_without_paths():
+    fk = copy.deepcopy(LinkPoints(chains(2), [4, 2], points(2), dtype=torch.float64))
+    q = torch.randn(10, dtype=torch.float64, device=G)
+    x = fk(q)
+    for k in ("_path", "_jtype", "_nq"):   # as stored before the kernels
+        del fk.__dict__[k]
+    assert torch.allclose(fk(q), x, rtol=0, atol=1e-13)
