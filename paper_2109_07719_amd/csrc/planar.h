@@ -17,9 +17,9 @@
 // to 50 links x 50 steps: 1.46 -> 0.54 and 4.57 -> 0.72 ms.
 //
 // The forward step (planar_qdd) of an FP32 handle works in link frames, as the
-// general kernels do, so its rounding errors are theirs.  The adjoint runs in FP64 in the
-// base frame, where the level loops only add, by the adjoint of the inverse
-// dynamics: with w = M^-1 (dt qd1_bar) (two sweeps with the step's factors),
+// general kernels do, so its rounding errors are theirs.  The adjoint runs in
+// FP64 in the base's axes, where the level loops turn nothing, by the adjoint of
+// the inverse dynamics: with w = M^-1 (dt qd1_bar) (two sweeps with the step's factors),
 //   tau_bar = w,  (q_bar, qd_bar) -= d/d(q, qd) <w, ID(q, qd, qdd)> at fixed qdd
 // (the derivative of M qdd + C(q, qd) = tau), in place of the reversed
 // statements of the three passes.  Sec. 3, Eq. adj_back; Sec. 4.1, Eq. adj_r.

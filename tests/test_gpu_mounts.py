@@ -50,7 +50,7 @@ def states(draws, dtype, K, ws=True):
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
-@pytest.mark.parametrize("name", ["trees", "balls", "quads"])
+@pytest.mark.parametrize("name", ["trees", "balls", "quads", "chains"])
 def test_forward_does_not_depend_on_the_mount_or_the_interval(name, dtype):
     print("case", name, dtype, flush=True)
     ref = states(FAMILIES[name], dtype, 1, ws=False)
@@ -72,7 +72,7 @@ def gradients(draws, dtype, K, tiling=None):
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
-@pytest.mark.parametrize("name", ["trees", "balls"])
+@pytest.mark.parametrize("name", ["trees", "balls", "chains"])
 @pytest.mark.parametrize("K,tiling", [(1, None), (1, (1, 1, False)), (3, None), (-2, None)])
 def test_gradients_do_not_depend_on_the_mount(name, dtype, K, tiling):
     print("case", name, dtype, K, tiling, flush=True)
