@@ -79,10 +79,10 @@ __device__ __forceinline__ S quad_sum(S x) {
   return x + quad<0x4E>(x);  // [2, 3, 0, 1]
 }
 
-// x / d by a reciprocal taken once, rounded as the division would be or, in
-// FP64, to the last bit or so.  FP32: by way of FP64.  FP64: 1 / d = hi + lo,
-// the two of one sign and not zero, so that x hi + x lo keeps its sign where x
-// is infinite or d zero.
+// x / d by a reciprocal taken once, rounded as the division would be.  FP32: by
+// way of FP64.  FP64: the product and its remainder, which rounds to the
+// quotient (Markstein's theorem); the last instruction is the division's own,
+// for zeros and infinities.
 template <typename S>
 struct Reciprocal;
 template <>
@@ -93,18 +93,15 @@ struct Reciprocal<float> {
 };
 template <>
 struct Reciprocal<double> {
-  double hi, lo;
-  __device__ __forceinline__ void set(double d) {
-    constexpr double eps2 = 2.2e-16 * 2.2e-16;
-    hi = 1.0 / d;
-    double r = fma(-d, hi, 1.0);
-    if (r < 0.0) {  // rounded away from zero: one unit back
-      hi = __longlong_as_double(__double_as_longlong(hi) - 1);
-      r = fma(-d, hi, 1.0);
-    }
-    lo = d == 0.0 ? hi : hi * (r > eps2 ? r : eps2);
+  double d, r;
+  __device__ __forceinline__ void set(double d_) {
+    d = d_;
+    r = fabs(d) < 0x1p-1022 ? copysign(0x1.fffffffffffffp1023, d) : 1.0 / d;  // (no infinite product)
   }
-  __device__ __forceinline__ double times(double x) const { return fma(x, lo, x * hi); }
+  __device__ __forceinline__ double times(double x) const {
+    const double q = x * r;
+    return __builtin_amdgcn_div_fixup(fma(fma(-d, q, x), r, q), d, x);
+  }
 };
 
 // A problem's columns and bounds on a lane of its quad
