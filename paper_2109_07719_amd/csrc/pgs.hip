@@ -22,7 +22,8 @@
 // too; the up to three rows past n are zero rows, which leave everything as it
 // is, and no branch separates one row's instructions from the next's.  The
 // sweep vectors go to the workspace as [niter + 1][n][batch].  Problems are
-// independent: no barriers.
+// independent: no barriers.  Problems of up to four rows that fill the chip
+// take a lane each (launch says from where on): G lanes per problem, 4 or 1.
 //
 // What bounds it: the instructions of a row, the GS order being a serial chain
 // of n niter rows.  With one lane per problem 32768 problems were 512
@@ -31,8 +32,7 @@
 // 32768 problems x 12 rows x 30 sweeps, FP32: solve 59 -> 29 us, adjoint 138
 // -> 71 us, and in FP64 71 -> 41 and 2033 -> 96; 64 problems 35 -> 17 and 93 ->
 // 33; 16 rows, 32768 problems, 92 -> 39 and 445 -> 113; 4 rows 18 -> 11 and 29
-// -> 20 (but 200000 problems of 4 rows, which fill the chip either way, 33 ->
-// 36 and 62 -> 91).
+// -> 18; 200000 problems of 4 rows 32 -> 29 and 60 -> 48.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -73,8 +73,10 @@ __device__ __forceinline__ double quad(double x) {
   return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true),
                           __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true));
 }
-template <typename S>
-__device__ __forceinline__ S quad_sum(S x) {
+// the sum over a problem's G lanes
+template <int G, typename S>
+__device__ __forceinline__ S lane_sum(S x) {
+  if constexpr (G == 1) return x;
   x += quad<0xB1>(x);  // [1, 0, 3, 2]
   return x + quad<0x4E>(x);  // [2, 3, 0, 1]
 }
@@ -104,27 +106,27 @@ struct Reciprocal<double> {
   }
 };
 
-// A problem's columns and bounds on a lane of its quad
-template <typename S, int N>
+// A problem's columns and bounds on one of its G lanes
+template <typename S, int N, int G>
 struct Problem {
-  static constexpr int C = N / 4;
+  static constexpr int C = N / G;
   int n, g;
   size_t p;
   S A[N][C];                  // off-diagonal; zero on the diagonal and past n
   S b[C], lo[C], hi[C];
   Reciprocal<S> inv[C];       // of A_jj
 
-  __device__ __forceinline__ size_t at(int c) const { return p * n + 4 * c + g; }
-  __device__ __forceinline__ bool has(int c) const { return 4 * c + g < n; }
-  __device__ __forceinline__ bool owns(int i) const { return g == i % 4 && i < n; }
+  __device__ __forceinline__ size_t at(int c) const { return p * n + G * c + g; }
+  __device__ __forceinline__ bool has(int c) const { return G * c + g < n; }
+  __device__ __forceinline__ bool owns(int i) const { return g == i % G && i < n; }
   __device__ __forceinline__ void load(S (&v)[C], const S* src, size_t first, size_t stride) const {
 #pragma unroll
-    for (int c = 0; c < C; ++c) v[c] = has(c) ? src[first + (4 * c + g) * stride] : S(0);
+    for (int c = 0; c < C; ++c) v[c] = has(c) ? src[first + (G * c + g) * stride] : S(0);
   }
   __device__ __forceinline__ void store(const S (&v)[C], S* dst, size_t first, size_t stride) const {
 #pragma unroll
     for (int c = 0; c < C; ++c)
-      if (has(c)) dst[first + (4 * c + g) * stride] = v[c];
+      if (has(c)) dst[first + (G * c + g) * stride] = v[c];
   }
   __device__ __forceinline__ Problem(const PgsArgs<S>& P, size_t p_, int g_) : n(P.n), g(g_), p(p_) {
     S d[C];
@@ -134,8 +136,8 @@ struct Problem {
     for (int i = 0; i < N; ++i)
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const S v = (i < n && has(c)) ? P.A[(p * n + i) * n + 4 * c + g] : S(0);
-        const bool diag = i == 4 * c + g;
+        const S v = (i < n && has(c)) ? P.A[(p * n + i) * n + G * c + g] : S(0);
+        const bool diag = i == G * c + g;
         A[i][c] = diag ? S(0) : v;
         if (diag && i < n) d[c] = v;
       }
@@ -151,26 +153,26 @@ struct Problem {
   __device__ __forceinline__ S row(int i, const S (&x)[C]) const {
     S d = S(0);
 #pragma unroll
-    for (int c = 0; c < C; ++c) d = fma(A[i][c], c == i / 4 && owns(i) ? S(0) : x[c], d);  // x_i may be infinite
-    d = quad_sum(d);
-    return over(-(b[i / 4] + d), i / 4);
+    for (int c = 0; c < C; ++c) d = fma(A[i][c], c == i / G && owns(i) ? S(0) : x[c], d);  // x_i may be infinite
+    d = lane_sum<G>(d);
+    return over(-(b[i / G] + d), i / G);
   }
 };
 
-template <typename S, int N>
+template <typename S, int N, int G>
 __global__ __launch_bounds__(kBlock) void k_pgs_solve(PgsArgs<S> P) {
-  constexpr int C = N / 4;
-  const size_t p = ((size_t)blockIdx.x * kBlock + threadIdx.x) / 4;
-  if (p >= (size_t)P.batch) return;  // whole quads
+  constexpr int C = N / G;
+  const size_t p = ((size_t)blockIdx.x * kBlock + threadIdx.x) / G;
+  if (p >= (size_t)P.batch) return;  // whole problems
   const size_t B = (size_t)P.batch, n = (size_t)P.n;
-  const Problem<S, N> m(P, p, threadIdx.x % 4);
+  const Problem<S, N, G> m(P, p, threadIdx.x % G);
   S x[C];
   m.load(x, P.x0, p * n, 1);
   for (int t = 0; t < P.niter; ++t) {
     if (P.ws) m.store(x, P.ws + p, t * n * B, B);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const int c = i / 4;
+      const int c = i / G;
       const S y = m.row(i, x);
       const S v = (y < m.lo[c]) ? m.lo[c] : ((y > m.hi[c]) ? m.hi[c] : y);
       x[c] = m.owns(i) ? v : x[c];
@@ -180,13 +182,13 @@ __global__ __launch_bounds__(kBlock) void k_pgs_solve(PgsArgs<S> P) {
   if (P.ws) m.store(x, P.ws + p, P.niter * n * B, B);
 }
 
-template <typename S, int N>
+template <typename S, int N, int G>
 __global__ __launch_bounds__(kBlock) void k_pgs_adjoint(PgsArgs<S> P) {
-  constexpr int C = N / 4;
-  const size_t p = ((size_t)blockIdx.x * kBlock + threadIdx.x) / 4;
-  if (p >= (size_t)P.batch) return;  // whole quads
+  constexpr int C = N / G;
+  const size_t p = ((size_t)blockIdx.x * kBlock + threadIdx.x) / G;
+  if (p >= (size_t)P.batch) return;  // whole problems
   const size_t B = (size_t)P.batch, n = (size_t)P.n;
-  const Problem<S, N> m(P, p, threadIdx.x % 4);
+  const Problem<S, N, G> m(P, p, threadIdx.x % G);
   // A_bar sums in FP64, from x widened once a sweep: its error does not grow
   // with the sweeps (relative error against FP64, 20 sweeps, 16 rows, FP32:
   // 1.15e-7 with FP32 sums, 6.9e-8 so, 7.2e-8 with the sums begun at the first
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(kBlock) void k_pgs_adjoint(PgsArgs<S> P) {
     if (t > 0) m.load(nx, P.ws + p, (t - 1) * n * B, B);
 #pragma unroll
     for (int i = N - 1; i >= 0; --i) {
-      const int c = i / 4;
+      const int c = i / G;
       const bool own = m.owns(i);
       const S y = m.row(i, x);
       const S t0 = own ? xb[c] : S(0);
@@ -225,8 +227,10 @@ __global__ __launch_bounds__(kBlock) void k_pgs_adjoint(PgsArgs<S> P) {
       const S own_db = -m.over(below || above ? S(0) : t0, c);
       bb[c] += own_db;
       Ad[c] += own ? own_db * y : S(0);
-      const S db = i % 4 == 0 ? quad<0x00>(own_db) : i % 4 == 1 ? quad<0x55>(own_db)
-                 : i % 4 == 2 ? quad<0xAA>(own_db) : quad<0xFF>(own_db);
+      S db = own_db;
+      if constexpr (G == 4)
+        db = i % 4 == 0 ? quad<0x00>(own_db) : i % 4 == 1 ? quad<0x55>(own_db)
+           : i % 4 == 2 ? quad<0xAA>(own_db) : quad<0xFF>(own_db);
 #pragma unroll
       for (int k = 0; k < C; ++k) {
         Ab[i][k] = fma(double(db), xd[k], Ab[i][k]);
@@ -242,7 +246,7 @@ __global__ __launch_bounds__(kBlock) void k_pgs_adjoint(PgsArgs<S> P) {
     if (i < P.n) {
 #pragma unroll
       for (int c = 0; c < C; ++c)
-        if (m.has(c)) P.Abar[(p * n + i) * n + 4 * c + m.g] = i == 4 * c + m.g ? Ad[c] : S(Ab[i][c]);
+        if (m.has(c)) P.Abar[(p * n + i) * n + G * c + m.g] = i == G * c + m.g ? Ad[c] : S(Ab[i][c]);
     }
   m.store(bb, P.bbar, p * n, 1);
   m.store(lb, P.lobar, p * n, 1);
@@ -268,20 +272,37 @@ int pgs_check(const char* who, int dtype, int batch, int n, int niter) {
   return SIM_OK;
 }
 
-// one kernel per row bucket (4, 8, 12, 16)
-template <typename S, int N>
-void launch_n(const PgsArgs<S>& a, hipStream_t st, bool adjoint, dim3 grid) {
-  if (adjoint) hipLaunchKernelGGL((k_pgs_adjoint<S, N>), grid, dim3(kBlock), 0, st, a);
-  else hipLaunchKernelGGL((k_pgs_solve<S, N>), grid, dim3(kBlock), 0, st, a);
+// SIMDs of the current device
+int simd_count() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 1024;
+  return 4 * cus;
+}
+
+// one kernel per row bucket (4, 8, 12, 16 with four lanes, 2 and 4 with one)
+template <typename S, int N, int G>
+void launch_n(const PgsArgs<S>& a, hipStream_t st, bool adjoint) {
+  const dim3 grid((unsigned)(((size_t)a.batch * G + kBlock - 1) / kBlock));
+  if (adjoint) hipLaunchKernelGGL((k_pgs_adjoint<S, N, G>), grid, dim3(kBlock), 0, st, a);
+  else hipLaunchKernelGGL((k_pgs_solve<S, N, G>), grid, dim3(kBlock), 0, st, a);
 }
 template <typename S>
 hipError_t launch(const PgsArgs<S>& a, hipStream_t st, bool adjoint) {
   if (a.batch == 0) return hipSuccess;
-  const dim3 grid((unsigned)(((size_t)a.batch * 4 + kBlock - 1) / kBlock));
-  if (a.n <= 4) launch_n<S, 4>(a, st, adjoint, grid);
-  else if (a.n <= 8) launch_n<S, 8>(a, st, adjoint, grid);
-  else if (a.n <= 12) launch_n<S, 12>(a, st, adjoint, grid);
-  else launch_n<S, 16>(a, st, adjoint, grid);
+  // One lane per problem for one or two rows (32768 problems of two, FP32, four
+  // lanes / one: solve 10 / 8 us, adjoint 19 / 9; 64 of them 8 / 8 and 12 / 8), and
+  // for up to four where four lanes would take more than one wavefront per SIMD
+  // (4 rows, 16384 problems 10 / 10 and 14 / 16, 24576 10 / 11 and 19 / 17, 200000
+  // 35 / 29 and 89 / 49; FP64 24576 16 / 13 and 27 / 20, 200000 70 / 46 and 133 /
+  // 80).  From five rows up A and A_bar no longer fit one lane's registers.
+  if (a.n <= 2) launch_n<S, 2, 1>(a, st, adjoint);
+  else if (a.n <= 4 && (size_t)a.batch * 4 > (size_t)kBlock * simd_count()) launch_n<S, 4, 1>(a, st, adjoint);
+  else if (a.n <= 4) launch_n<S, 4, 4>(a, st, adjoint);
+  else if (a.n <= 8) launch_n<S, 8, 4>(a, st, adjoint);
+  else if (a.n <= 12) launch_n<S, 12, 4>(a, st, adjoint);
+  else launch_n<S, 16, 4>(a, st, adjoint);
   return hipGetLastError();
 }
 
