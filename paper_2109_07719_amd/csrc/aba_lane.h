@@ -197,12 +197,33 @@ ABA_HD V6<S> p3_accel(const LinkC<S>& L, Tape<S>& t, const V6<S>& apar) {
 }
 
 // ------------------------------------------------------- free-floating root
-// 6x6 SPD factorisation (lower Cholesky, packed rows, the diagonal as its
-// reciprocal: six divisions in place of 27, a tenth of a quadruped's forward
-// step)
+// a / d for several a: by 1 / d taken once, the product and its remainder, which
+// rounds to the quotient (Markstein's theorem), for real numbers; other scalars
+// divide.
+template <typename S>
+ABA_HD S reciprocal(const S& d) {
+  return d;  // (not used)
+}
+ABA_HD float reciprocal(const float& d) { return 1.0f / d; }
+ABA_HD double reciprocal(const double& d) { return 1.0 / d; }
+template <typename S>
+ABA_HD S quotient(const S& a, const S& d, const S&) {
+  return a / d;
+}
+ABA_HD float quotient(const float& a, const float& d, const float& inv) {
+  const float q = a * inv;
+  return __builtin_fmaf(__builtin_fmaf(-d, q, a), inv, q);
+}
+ABA_HD double quotient(const double& a, const double& d, const double& inv) {
+  const double q = a * inv;
+  return __builtin_fma(__builtin_fma(-d, q, a), inv, q);
+}
+// 6x6 SPD factorisation (lower Cholesky, packed rows), and the reciprocals of
+// its diagonal: six divisions in place of 27, a tenth of a quadruped's forward
+// step
 template <typename S>
 struct Chol6 {
-  S L[21];  // the diagonal is not set
+  S L[21];
   S inv[6];
 };
 template <typename S>
@@ -230,10 +251,12 @@ ABA_HD Chol6<S> chol6(const SySp<S>& M) {
       S s = A[6 * i + j];
 #pragma unroll
       for (int k = 0; k < j; ++k) s = s - f.L[i * (i + 1) / 2 + k] * f.L[j * (j + 1) / 2 + k];
-      if (i == j)
-        f.inv[i] = S(1) / sqrt(s);
-      else
-        f.L[i * (i + 1) / 2 + j] = s * f.inv[j];
+      if (i == j) {
+        f.L[i * (i + 1) / 2 + i] = sqrt(s);
+        f.inv[i] = reciprocal(f.L[i * (i + 1) / 2 + i]);
+      } else {
+        f.L[i * (i + 1) / 2 + j] = quotient(s, f.L[j * (j + 1) / 2 + j], f.inv[j]);
+      }
     }
   }
   return f;
@@ -246,14 +269,14 @@ ABA_HD V6<S> chol6_solve(const Chol6<S>& f, const V6<S>& b) {
     S s = x[i];
 #pragma unroll
     for (int k = 0; k < i; ++k) s = s - f.L[i * (i + 1) / 2 + k] * x[k];
-    x[i] = s * f.inv[i];
+    x[i] = quotient(s, f.L[i * (i + 1) / 2 + i], f.inv[i]);
   }
 #pragma unroll
   for (int i = 5; i >= 0; --i) {
     S s = x[i];
 #pragma unroll
     for (int k = i + 1; k < 6; ++k) s = s - f.L[k * (k + 1) / 2 + i] * x[k];
-    x[i] = s * f.inv[i];
+    x[i] = quotient(s, f.L[i * (i + 1) / 2 + i], f.inv[i]);
   }
   return v6<S>(v3<S>(x[0], x[1], x[2]), v3<S>(x[3], x[4], x[5]));
 }
