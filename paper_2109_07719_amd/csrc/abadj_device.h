@@ -825,12 +825,11 @@ __device__ __forceinline__ void integrate_lane(State<S, FREE>& st, const Lane& l
   }
 }
 
-// Whether the rollouts of a variant take the planar step.  A handle whose
-// reverse runs in FP32 (R) keeps the general one: its store-all forward does,
-// whose tape holds the general step's intermediates, and in FP32 two steps
-// that round differently show between its checkpointing schemes.
-template <int FR, bool CHAIN, typename R>
-constexpr bool kPlanarStep = CHAIN && FR == kFrIdentity && sizeof(R) == sizeof(double);
+// Whether a variant's steps are planar: those of its rollouts under every
+// checkpointing scheme, of the replays and of single evaluations, whatever the
+// reverse passes' type, so that all of them round alike.
+template <int FR, bool CHAIN>
+constexpr bool kPlanarStep = CHAIN && FR == kFrIdentity;
 
 // The constants a forward step reads, loaded once (inside the time loop a
 // store could alias them, and every step would wait for them).
@@ -874,7 +873,7 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_aba(AbaArgs<S> A)
     tau = load_ctl<BALL>(A.tau, l);
   }
   Step<S> o;
-  if constexpr (CHAIN && FR == kFrIdentity)
+  if constexpr (kPlanarStep<FR, CHAIN>)
     o.t.qdd = planar_qdd<S>(gravity(A.P), planar_const<S>(A.P, l), st.q[0], st.qd[0], tau.x, maxd);
   else
     aba_wave<S, FREE, CHAIN, BALL>(gravity(A.P), l, L, st, limit_tau<FR>(A.P, l, st, tau), maxd, xb, o);
@@ -905,10 +904,12 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_aba(AbaArgs<S> A)
 // Forward rollout.  MODE 0: plain; 1: store the initial state of every
 // K-th step; 2: store every step's initial state and intermediates
 // (store-all).  With a trajectory buffer, also write x^{t+1} for every step.
-// R: the type of the handle's reverse passes (kPlanarStep).
-template <typename S, typename R, bool FREE, int FR, bool CHAIN, int MODE>
+// Planar chains move by the planar step then too; what is stored for the
+// reverse are the general step's intermediates at the same state (forward, 4096
+// chains of 7 links x 200 steps, K = 0: 1175 -> 1477 us).
+template <typename S, bool FREE, int FR, bool CHAIN, int MODE>
 __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_forward(FwdArgs<S> A) {
-  constexpr bool PLANAR = kPlanarStep<FR, CHAIN, R> && MODE != 2;
+  constexpr bool PLANAR = kPlanarStep<FR, CHAIN>;
   S* xb = CHAIN ? nullptr : lds<S>() + wave_in_block() * (XB * kWave);
   const int wb = wave_batch();
   const Lane l = load_lane(A.P, wb);
@@ -937,8 +938,9 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_forward(FwdArgs<S
         S* row = A.ck + (size_t)t * (RW + (size_t)kTapeFields * ns);
         put_slot(st, row, ns, nf, l.slot, l.fidx);
         put_tape(o, row + RW, ns, l.slot);
-        integrate_lane<S, FREE, BALL>(st, l, o, A.dt);
+        if constexpr (!PLANAR) integrate_lane<S, FREE, BALL>(st, l, o, A.dt);
       }
+      if constexpr (PLANAR) advance<FR, CHAIN, PLANAR>(A.P, gravity(A.P), l, SC, st, tau, A.dt, maxd, xb);
     } else {
       advance<FR, CHAIN, PLANAR>(A.P, gravity(A.P), l, SC, st, tau, A.dt, maxd, xb);
     }
@@ -1275,7 +1277,7 @@ __attribute__((amdgpu_waves_per_eu(FRAME ? (FREE ? 1 : 2) : (FREE || sizeof(R) >
   const int nf = A.P.nfree;
   const LinkC<S> L = load_linkc<S, FR>(A.P, l);
   const LinkC<R> LR = widen<R>(L);
-  constexpr bool PLANAR = kPlanarStep<FR, CHAIN, R>;
+  constexpr bool PLANAR = kPlanarStep<FR, CHAIN>;
   const auto SC = step_const<PLANAR>(A.P, l, L);
   int nonfin = 0;  // non-finite outputs
   ParamBar<R> pg;
@@ -1513,7 +1515,7 @@ __global__ __launch_bounds__(kWave * kMaxWavesPerBlock) void k_forward_jvp(JvpAr
   const Lane l = load_lane(A.P, wb);
   const int maxd = wave_maxd(A.P, wb);
   const int nu = A.P.nu;
-  constexpr bool PLANAR = CHAIN && FR == kFrIdentity;
+  constexpr bool PLANAR = kPlanarStep<FR, CHAIN>;
   const auto SC = step_const<PLANAR>(A.P, l, dual_const(load_linkc<S, FR>(A.P, l)));
   const V3<D> g = v3<D>(D(A.P.g[0], S(0)), D(A.P.g[1], S(0)), D(A.P.g[2], S(0)));
   const D dt = D(A.dt, S(0));
@@ -1593,24 +1595,17 @@ hipError_t launch_aba_v(const AbaArgs<S>& a, const Tiling& tl, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <typename S, typename R, bool F, int E, bool C>
-hipError_t launch_forward_r(const FwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
+template <typename S, bool F, int E, bool C>
+hipError_t launch_forward_v(const FwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
+  if (a.P.nwaves == 0) return hipSuccess;
   const int mode = (a.ck == nullptr) ? 0 : (a.K == 0) ? 2 : 1;
   size_t lds = 0;
   const int w = single_wpb<S, C>(tl, a.P.nwaves, lds);
   const dim3 grid(a.P.nwaves / w), block(kWave * w);
-  if (mode == 0) hipLaunchKernelGGL((k_forward<S, R, F, E, C, 0>), grid, block, lds, st, a);
-  else if (mode == 1) hipLaunchKernelGGL((k_forward<S, R, F, E, C, 1>), grid, block, lds, st, a);
-  else hipLaunchKernelGGL((k_forward<S, double, F, E, C, 2>), grid, block, lds, st, a);
+  if (mode == 0) hipLaunchKernelGGL((k_forward<S, F, E, C, 0>), grid, block, lds, st, a);
+  else if (mode == 1) hipLaunchKernelGGL((k_forward<S, F, E, C, 1>), grid, block, lds, st, a);
+  else hipLaunchKernelGGL((k_forward<S, F, E, C, 2>), grid, block, lds, st, a);
   return hipGetLastError();
-}
-template <typename S, bool F, int E, bool C>
-hipError_t launch_forward_v(const FwdArgs<S>& a, const Tiling& tl, hipStream_t st) {
-  if (a.P.nwaves == 0) return hipSuccess;
-  if constexpr (kPlanarStep<E, C, double> && sizeof(S) == sizeof(float)) {
-    if (!a.adj64) return launch_forward_r<S, float, F, E, C>(a, tl, st);
-  }
-  return launch_forward_r<S, double, F, E, C>(a, tl, st);
 }
 
 // SIMDs of the current device.

@@ -59,7 +59,6 @@ struct FwdArgs {
   S* ck;         // nullable: K >= 1 checkpoints [ceil(T/K)][state width][nslots];
                  // K == 0 every step's state and intermediates
                  // [T][state width + kTapeFields][nslots]
-  int adj64 = 1; // S = float: the handle's reverse passes run in FP64
 };
 
 template <typename S>

@@ -803,7 +803,6 @@ int sim_forward(sim_t h, const void* q0, const void* qd0, const void* tau, doubl
     a.qdT = (float*)qdT;
     a.traj = (float*)traj;
     a.ck = (float*)workspace;
-    a.adj64 = h->adj_dtype == SIM_F64 ? 1 : 0;
     e = aba::launch_forward(a, shape(h), h->tiling, (hipStream_t)stream);
   }
   if (e != hipSuccess) return fail(SIM_ERR_HIP, std::string("sim_forward: launch failed: ") + hipGetErrorString(e));
