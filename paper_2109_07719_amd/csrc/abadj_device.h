@@ -1658,12 +1658,12 @@ hipError_t launch_backward_one(const BwdArgs<S>& a, const Tiling& tl, hipStream_
 
 // The pipelined base-frame adjoint, if its LDS fits and the batches take at
 // most `rounds` rounds of resident workgroups (0: any number).
-template <typename S, bool F, int E, int NP, int NR>
+template <typename S, bool F, int E, bool C, int NP, int NR>
 bool launch_frame_pipe(const BwdArgs<S>& a, size_t rounds, hipStream_t st) {
   const size_t lds = FramePipe<S, F, E, NP, NR>::lds(a.K, a.P.mfree), limit = lds_limit();
   if (lds > limit) return false;
   if (rounds > 0 && (size_t)a.P.nwaves > rounds * (simd_count() / 4) * (limit / lds)) return false;
-  hipLaunchKernelGGL((k_backward_frame_pipe<S, F, E, NP, NR>), dim3(a.P.nwaves), dim3((NP + NR + 1) * kWave), lds, st, a);
+  hipLaunchKernelGGL((k_backward_frame_pipe<S, F, E, C, NP, NR>), dim3(a.P.nwaves), dim3((NP + NR + 1) * kWave), lds, st, a);
   return true;
 }
 template <typename S, bool F, int E, bool C>
@@ -1680,10 +1680,10 @@ hipError_t launch_backward_frame(const BwdArgs<S>& a, const Tiling& tl, hipStrea
   // trees, 384 844 / 688 / -, 744 885 / 1089 / -).  One step has nothing to
   // overlap.
   if (a.K == 1 && a.T > 1 && (!tl.chosen || tl.pipelined)) {
-    if (launch_frame_pipe<S, F, E, 2, 0>(a, 1, st) || launch_frame_pipe<S, F, E, 1, 0>(a, tl.chosen ? 0 : 1, st))
+    if (launch_frame_pipe<S, F, E, C, 2, 0>(a, 1, st) || launch_frame_pipe<S, F, E, C, 1, 0>(a, tl.chosen ? 0 : 1, st))
       return hipGetLastError();
   }
-  if (a.K > 1 && a.T > 1 && (launch_frame_pipe<S, F, E, 2, 1>(a, 2, st) || launch_frame_pipe<S, F, E, 1, 1>(a, 2, st)))
+  if (a.K > 1 && a.T > 1 && (launch_frame_pipe<S, F, E, C, 2, 1>(a, 2, st) || launch_frame_pipe<S, F, E, C, 1, 1>(a, 2, st)))
     return hipGetLastError();
   return launch_backward_one<S, double, F, E, C, false, true>(a, tl, st);
 }

@@ -714,7 +714,9 @@ struct FramePipe {
 // bounds K == 1, the replaying one K > 1.  Adjoints, one wavefront / one
 // producer / two: 1024 quadrupeds x 200 steps in segments of 10, 2.86 / 1.24 /
 // 1.16 ms; 1024 ball-jointed ones x 100 steps, K = 1, 1.22 / 0.70 / 0.60.
-template <typename S, bool FREE, int FR, int NP, int NR>
+// CHAIN: the replay takes the register exchange of the chain kernels, as the
+// rollout did.
+template <typename S, bool FREE, int FR, bool CHAIN, int NP, int NR>
 __global__ __launch_bounds__((NP + NR + 1) * kWave)
 __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(BwdArgs<S> A) {
   using P = FramePipe<S, FREE, FR, NP, NR>;
@@ -766,7 +768,7 @@ __attribute__((amdgpu_waves_per_eu(FREE ? 1 : 2))) void k_backward_frame_pipe(Bw
         }
         if (i + 1 < length(c)) {
           const V3<S> tau = act ? load_ctl<BALL>(A.tau + (size_t)(t0 + i) * nu, l) : zero3<S>();
-          advance<FR, false, false>(A.P, gravity(A.P), l, L, st, tau, A.dt, maxd, xreplay);
+          advance<FR, CHAIN, false>(A.P, gravity(A.P), l, L, st, tau, A.dt, maxd, xreplay);
           if (act) put_slot(st, base + (size_t)(i + 1) * sw, kWave, mf, l.lane, rl);
         }
       }
