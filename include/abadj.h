@@ -213,11 +213,12 @@ int sim_status(sim_t h, void *stream, int *nonfinite_count);
  *     recomputes step t-1 while another reverses step t), 0 = one wavefront
  *     does both.
  * A choice whose LDS would exceed the device's per-workgroup limit is
- * reduced at launch.  Default (from occupancy): 4 waves per block;
+ * reduced at launch.  Default (from occupancy): one wave per block;
  * pipelined with 2 pairs per block while the pipelined pairs fit one
- * wavefront per SIMD, otherwise not pipelined.  Until a tiling is set or
- * tuned, kernels with rules of their own go by those (one wavefront per
- * block; the FP64 adjoints by the number of batches).  Not thread-safe against
+ * wavefront per SIMD, otherwise not pipelined.  The default values stand for
+ * the kernels' own rules, which the FP64 adjoints have (by the number of
+ * batches and their LDS): sim_get_tiling reports them until others are set or
+ * tuned, and setting them brings the rules back.  Not thread-safe against
  * concurrent launches on the same handle.  Errors: SIM_ERR_INVALID_ARG. */
 typedef struct {
   int32_t waves_per_block;

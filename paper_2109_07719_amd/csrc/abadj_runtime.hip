@@ -78,12 +78,13 @@ struct sim_handle {
 
 namespace {
 
-// Launch geometry before any tuning, from occupancy alone.  While the
-// producer/consumer pairs of the pipelined adjoint fit one wavefront per
-// SIMD, the adjoint is pipelined with two pairs per workgroup (a workgroup
-// spreads its wavefronts over the CU's SIMDs, while separate one-pair
-// workgroups on one CU may share SIMDs); beyond that the pipelining only
-// oversubscribes the SIMDs and one wavefront per step is used.
+// Launch geometry before any tuning, from occupancy alone, where a kernel has
+// no rule of its own (single_wpb, launch_backward_planar,
+// launch_backward_frame).  While the producer/consumer pairs of the pipelined
+// adjoint fit one wavefront per SIMD, the adjoint is pipelined with two pairs
+// per workgroup (a workgroup spreads its wavefronts over the CU's SIMDs, while
+// separate one-pair workgroups on one CU may share SIMDs); beyond that the
+// pipelining only oversubscribes the SIMDs and one wavefront per step is used.
 aba::Tiling default_tiling(int nwaves) {
   aba::Tiling t;
   int dev = 0, cus = 256;
@@ -92,7 +93,7 @@ aba::Tiling default_tiling(int nwaves) {
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
   }
   const int simds = 4 * cus;
-  t.waves_per_block = 4;
+  t.waves_per_block = 1;
   t.pipelined = 2 * nwaves <= simds;
   t.pairs_per_block = 2;
   return t;
@@ -687,7 +688,9 @@ int sim_set_tiling(sim_t h, const sim_tiling_t* t) {
   h->tiling.waves_per_block = w;
   h->tiling.pairs_per_block = p;
   h->tiling.pipelined = t->pipelined != 0;
-  h->tiling.chosen = true;
+  // the values that stand for the kernels' own rules bring those back
+  const aba::Tiling own = default_tiling(h->nwaves);
+  h->tiling.chosen = w != own.waves_per_block || p != own.pairs_per_block || h->tiling.pipelined != own.pipelined;
   return SIM_OK;
 }
 
