@@ -111,7 +111,9 @@ typedef struct {
 
 /* Per-link model parameters (host arrays, double precision). */
 typedef struct {
-  const double *E_T;      /* [9 n_links] row-major rotation parent->joint   */
+  const double *E_T;      /* [9 n_links] row-major rotation parent->joint (any
+                             matrix is taken as it is, by slower adjoints where
+                             it is no rotation to the dtype's rounding)      */
   const double *r_T;      /* [3 n_links] joint origin, parent coordinates   */
   const double *axis;     /* [3 n_links] unit joint axis, link coordinates  */
   const double *mass;     /* [n_links] > 0                                  */
@@ -177,16 +179,20 @@ int sim_get_info(sim_t h, sim_info_t *out);
  * and forward rollout in FP32 (segment replays for K > 1 and binomial
  * advances also run the FP32 step, so they reproduce the forward's states
  * bit for bit).  With SIM_F64 (the default) each step's intermediates are
- * recomputed in FP64 from the exactly widened FP32 state and control, the
- * reverse sweeps through the adjoints of the integrator and the three ABA
- * passes run in FP64, and so does the adjoint state carried from step to
- * step; the outputs are rounded to FP32 once.  The result is the gradient
- * of the step map along the FP32 trajectory to FP64 round-off (store-all,
- * K == 0, reverses the FP32 intermediates it stored).  SIM_F32 runs the
- * whole backward pass in FP32: faster, but on long chains and chaotic
- * rollouts the reverse recursion loses digits (gradient errors of 1e-3 and
- * more).  FP64 handles accept SIM_F64 only.  Takes effect for later
- * sim_backward calls (and graphs captured after the change).  Errors:
+ * recomputed in FP64 from the exactly widened FP32 state and control, its
+ * adjoint is formed in FP64, and so is the adjoint state carried from step to
+ * step; the outputs are rounded to FP32 once.  The adjoint of a step is that
+ * of the inverse dynamics, ID(q, qd, qdd) = tau, at the step's acceleration
+ * (with joint frames rounded to FP32 taken as the rotations next to them), or,
+ * for model-parameter gradients, K == 0 and joint frames that are no rotations
+ * to the type's rounding, the adjoints of the integrator and the three ABA
+ * passes in reverse.  Either way the result is the gradient of the step along
+ * the FP32 trajectory to FP64 round-off and the rounding of the joint frames
+ * (store-all, K == 0, reverses the FP32 intermediates it stored).  SIM_F32
+ * runs the whole backward pass in FP32, by those reversed passes: on long
+ * chains and chaotic rollouts their recursion loses digits (gradient errors
+ * of 1e-3 and more).  FP64 handles accept SIM_F64 only.  Takes effect for
+ * later sim_backward calls (and graphs captured after the change).  Errors:
  * SIM_ERR_INVALID_ARG (null handle), SIM_ERR_UNSUPPORTED_DTYPE. */
 int sim_set_adjoint_dtype(sim_t h, int dtype);
 
@@ -289,7 +295,9 @@ int sim_checkpoint_schedule(int T, int s, int32_t *actions, int capacity, int *n
  * App. B), or with K == 0 every step's state and intermediates (store-all,
  * the memory-hungry alternative the checkpointing replaces), or with K < 0
  * (binomial checkpointing) only x^0;
- * workspace == NULL runs the plain forward pass (nothing stored).
+ * workspace == NULL runs the plain forward pass (nothing stored).  States
+ * are the same bit for bit whatever K != 0 and whatever is stored; K == 0 is
+ * a kernel of its own, and may round the last place otherwise.
  * Errors: SIM_ERR_INVALID_ARG (T < 0, K < -4096, dt not finite or <= 0,
  * null required pointer), SIM_ERR_WORKSPACE_TOO_SMALL, SIM_ERR_HIP. */
 int sim_forward(sim_t h, const void *q0, const void *qd0, const void *tau, double dt, int T, int K,
@@ -385,7 +393,9 @@ int sim_aba(sim_t h, const void *q, const void *qd, const void *tau, void *qdd, 
  * (one add, subtract, multiply, divide, square root, sine or cosine = 1),
  * counted by running the per-link arithmetic once with an operation-
  * counting scalar type.  kind: 0 = one ABA evaluation, 1 = one forward
- * step (ABA + integration), 2 = one backward step (recompute + adjoint). */
+ * step (ABA + integration), 2 = one backward step (recompute + adjoint).
+ * Counted are the passes in link frames and their reversed statements; the
+ * kernels of planar chains and of the FP64 adjoint take fewer. */
 int sim_flops(sim_t h, int kind, double *flops_per_step);
 
 /* Thread-local description of the last error on this thread ("" if none). */
@@ -412,8 +422,7 @@ const char *sim_last_error(void);
 
 /* Bytes of the workspace that keeps x at the start of every sweep (and the
  * result) for the adjoint: (niter + 1) * n * batch * sizeof(dtype), and for
- * n >= 13 another niter * n * batch elements after them (scratch of the
- * adjoint; the sweep vectors stay as they are). */
+ * n >= 13 another niter * n * batch elements after them (no longer used). */
 int sim_pgs_workspace_bytes(int dtype, int batch, int n, int niter, size_t *bytes);
 
 /* Solve.  workspace (nullable): when given (workspace_bytes at least
@@ -439,7 +448,8 @@ int sim_pgs_adjoint(int dtype, int batch, int n, int niter, const void *A, const
  * link of path[s], from the joint coordinates q (the loss side of Sec. 3, Eq.
  * diff_u); the adjoint writes dL/dq of <xbar, x> into the entries of gq that
  * belong to the paths' joints (the caller clears gq: other entries keep their
- * values).  All arrays are DEVICE arrays of the dtype, contiguous: path [n_sys]
+ * values; no two paths may share a link, of two writes one is lost).  All
+ * arrays are DEVICE arrays of the dtype, contiguous: path [n_sys]
  * [len] int32 links (root first, -1 past the end, len <= SIM_MAX_LINKS, a free
  * root only first), jtype [n_links] int32 (SIM_JOINT_*), qidx [n_links] int64
  * (the joint's first entry of q), ETt [n_links][9] (E_T transposed), rT and ax
@@ -481,14 +491,15 @@ int sim_link_points_adjoint(int dtype, int n_sys, int len, const int32_t *path, 
  *
  * Per-system parameters (DEVICE, dtype, [nparams][batch], entry k of
  * system s at k * batch + s): per link i at 25 i: E_T (9, row-major, parent
- * -> joint frame), r_T (3, joint origin in the parent frame), axis (3, any
+ * -> joint frame; the rotation next to it is taken), r_T (3, joint origin in the parent frame), axis (3, any
  * nonzero length: the joint moves along axis / |axis|), mass, com (3, link
  * frame), inertia about the com (xx, yy, zz, xy, xz, yz); then per sphere k
  * at 25 n + 4 k: centre (3, link frame), radius.
  *
  * States are DEVICE arrays of the dtype, entry-major: q [nq][batch], qd
  * [nv][batch], tau [T][nu][batch]; a free root's q is (p_world, quat x, y,
- * z, w), its qd the body-frame (w, v).  Calls only enqueue work on `stream`
+ * z, w), its qd the body-frame (w, v).  The quaternion has unit length, as
+ * the step leaves it.  Calls only enqueue work on `stream`
  * (NULL = default): no allocation, no synchronisation.  Errors:
  * SIM_ERR_INVALID_ARG, SIM_ERR_INVALID_TOPOLOGY, SIM_ERR_UNSUPPORTED_DTYPE,
  * SIM_ERR_HIP; sim_last_error() describes the failure. */

@@ -38,7 +38,8 @@
 // solve, FP32 states): a rollout step 30 us (590 us with one lane per system
 // and its records in LDS), a gradient step 107 us (3.1 ms, records in private
 // memory); of these the sweeps are 11 and 30 us.  250 systems in FP64: 26 us
-// and 88 us (520 us and 2.5 ms).
+// and 60 us, by the kernel of two wavefronts per four systems (520 us and
+// 2.5 ms).
 #pragma once
 
 #include <utility>

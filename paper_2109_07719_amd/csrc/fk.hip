@@ -16,9 +16,9 @@
 // adjoint's, where a tree level at a time took about 30 launches a level,
 // 45 ms in all.  A scan over the lanes would be shorter, but rounds in
 // another order: the seeds of ill-conditioned chains amplify that (up to
-// 3e-5 in the gradient over 50 steps in FP32).  Sums of three products run in index order by
-// fused multiply-adds, everything else rounds operation by operation, as the
-// torch expressions of the same module do.
+// 3e-5 in the gradient over 50 steps in FP32).  So the products keep the torch
+// expressions' order; their sums of three are fused multiply-adds in index
+// order, where a library's product may round otherwise.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>

@@ -31,8 +31,9 @@ def _ptr(t):
 def _stream():
     """The current stream's handle.  Not torch.cuda.current_stream(), which
     makes a Stream object: 13 to 18 us of a one-step rollout's 147 in each
-    direction, against 0.3 for the handle alone (one step of 4096 quadrupeds
-    with its gradient 145 -> 55 us)."""
+    direction, against 0.3 for the handle alone.  (One step of 4096 quadrupeds
+    with its gradient: 145 -> 110 us, or 66 -> 55 in runs where autograd's
+    thread wakes at once.)"""
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
